@@ -121,3 +121,42 @@ def test_variant_argument_checks():
     assert st == P._abi.TAG_ESHAPE
     del w
     g.close()
+
+
+@pytest.mark.parametrize("n_op,n_dev,R,f,heads,relations,edge_act,heads_mode", [
+    (64, 2, 2, 64, 64, 5, "affine", "concat"),     # device rows at the length that is walked whole; one channel per head
+    (65, 2, 2, 64, 32, 5, "affine", "concat"),     # ... one entry longer: two parts
+    (1030, 3, 1, 128, 16, 3, "relu", "concat"),    # sixteen parts, the last short
+    (130, 3, 2, 256, 64, 5, "affine", "concat"),   # four heads per lane
+    (130, 3, 2, 256, 1, 5, "affine", "avg"),
+    (130, 3, 2, 256, 8, 3, "affine", "avg"),
+    (3307, 2, 20, 64, 4, 5, "affine", "concat"),   # several rows per lane group, a ragged last group
+])
+def test_variant_row_parts_and_groups(n_op, n_dev, R, f, heads, relations, edge_act, heads_mode):
+    # ops linked to device 0 only, to all, or to none; the last device has few links (fewer parts than the first)
+    od = [(u, j) for u in range(n_op) for j in range(n_dev) if j == 0 or (u % 3 == 0 and j < n_dev - 1) or u == 5]
+    topo = mk_topo(n_op, n_dev, oo=[(i, i + 1) for i in range(n_op - 1) if i % 7], dd=[(0, 1)], od=od)
+    err = _run(topo, R, f, heads, 2, relations, edge_act, heads_mode, seed=n_op, shared_oo=relations == 3)
+    say(f"n_op={n_op} R={R} f={f} K={heads} {relations} {edge_act} {heads_mode}: {err:.2e}")
+
+
+def test_variant_union_of_topologies():
+    # replicas of two unlike topologies: row ranges cross both topology and replica ends
+    topos = [mk_topo(n, m, oo=[(i, i + 2) for i in range(n - 2)], dd=[(0, m - 1)],
+                     od=[(u, j) for u in range(n) for j in range(m) if (u + j) % 3]) for n, m in ((71, 2), (150, 5))]
+    f, K, L, R = 128, 4, 2, 3
+    w = synth.make_weights(f, K, L, 42, f, bias_scale=0.3, relations=5)
+    parts = [_features(t, R, 11 + i, False) for i, t in enumerate(topos)]
+    cat = [np.concatenate([p[k] for p in parts], axis=1) for k in range(5)]
+    g = P.Graph(topos)
+    m = P.Model(w, f=f, heads=K, layers=L, f_op=42, relations=5)
+    E_op, E_dev = P.forward(g, m, *(dev_tensor(a) for a in cat))
+    o = d = 0
+    for t, x in zip(topos, parts):
+        for r in range(R):
+            R_op, R_dev = oracle.forward(t, x[0][r], x[1][r], x[2][r], x[3][r], x[4][r], w, f=f, heads=K, layers=L,
+                                         relations=5, edge_act="affine", heads_mode="concat")
+            got = np.vstack([E_op[r, o:o + t.n_op].cpu().numpy(), E_dev[r, d:d + t.n_dev].cpu().numpy()])
+            assert row_rel_err(got, np.vstack([R_op, R_dev])) <= FP32_TOL
+        o, d = o + t.n_op, d + t.n_dev
+    g.close()
