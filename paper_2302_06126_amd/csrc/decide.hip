@@ -95,6 +95,10 @@ __global__ void dec_query_rows(DecArgs A, int32_t *qrow) {
     }
 }
 
+// max(x, 0) of a value in [-1, 1]: folds into the clamp bit of the
+// instruction that makes x
+__device__ __forceinline__ float clamp01(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, 1.f); }
+
 constexpr int kScoreThreads = 256;
 
 __device__ __forceinline__ float slice_score(const DecArgs &A, const float *urg, const float *vq,
@@ -558,6 +562,20 @@ __global__ void __launch_bounds__(256) dec_full(FullArgs FA) {
 // lanes; the t row of j, the option bases and w2 are wave-uniform LDS reads.
 constexpr int kFullRun = 16;
 
+// The exponent e >= 0 that brings values of magnitude <= b (finite), and the
+// rounding of their sums, into [-1, 1] when they are scaled by 2^-e.
+__device__ __forceinline__ int relu_exponent(float b) {
+    int e = 0;
+    frexpf(b, &e);
+    return max(e + 1, 0);
+}
+// whether a unit with pre-activations of magnitude <= b and readout weight w
+// may be scaled so: false for infinities, NaN and sizes where 2^-e b or 2^e w
+// would leave the normal range
+__device__ __forceinline__ bool relu_scalable(float b, float w) {
+    return b < 0x1p40f && fabsf(w) < 0x1p80f;
+}
+
 struct FullTpm {
     FullArgs FA;
     const float *base;     // [Q][4][HP]: W1_opt + b1 + v_q (zero past H)
@@ -587,17 +605,66 @@ __global__ void __launch_bounds__(256) dec_full_tpm(FullTpm T) {
     // as LDS broadcasts in the inner loops
     __shared__ float sbq[4 * HP], sw2[HP], strow[16 * HP];
     for (int i = threadIdx.x; i < 4 * HP; i += 256) sbq[i] = T.base[(int64_t)q * 4 * HP + i];
-    for (int i = threadIdx.x; i < HP; i += 256) sw2[i] = T.w2p[i];
     for (int i = threadIdx.x; i < nd * HP; i += 256) {
         const int j = i / HP, h = i % HP;
         strow[i] = h < H ? A.t[((int64_t)r * A.n_dev + d0 + j) * H + h] : 0.f;
+    }
+    __syncthreads();
+    // Each hidden unit's pre-activations are scaled by a power of two that
+    // brings all of them (sums of its t rows plus a base) into [-1, 1], and
+    // its readout weight by the inverse, both exactly, so that the ReLU is the
+    // clamp of the add: add, multiply-add per (mask, option, unit) instead of
+    // add, max, multiply-add, with the same bits (64 queries of 16 devices, H
+    // = 128, 2.1 G mask-units: 210 -> 190 us, vector issue about 75% of it,
+    // the rest the LDS broadcasts of w2, the bases and the t row).
+    bool ok = true;
+    float b = 0.f;
+    static_assert(HP <= 256, "one hidden unit per thread");
+    if (threadIdx.x < HP) {
+        const int h = threadIdx.x;
+        for (int o = 0; o < 4; ++o) b += fabsf(sbq[o * HP + h]);   // (a NaN stays)
+        for (int j = 0; j < nd; ++j) b += fabsf(strow[j * HP + h]);
+        ok = relu_scalable(b, T.w2p[h]);
+    }
+    const bool fast = __syncthreads_and(ok);   // (else ReLU as a max, unscaled)
+    if (threadIdx.x < HP) {
+        const int h = threadIdx.x, e = fast ? relu_exponent(b) : 0;
+        for (int o = 0; o < 4; ++o) sbq[o * HP + h] = ldexpf(sbq[o * HP + h], -e);
+        for (int j = 0; j < nd; ++j) strow[j * HP + h] = ldexpf(strow[j * HP + h], -e);
+        sw2[h] = ldexpf(T.w2p[h], e);
     }
     __syncthreads();
     const float *trow = strow;
     const float *bq = sbq;
     float m = -INFINITY, z = 0.f;
     int32_t im = INT32_MAX;
-    if (g0 < total) {
+    auto put = [&](uint32_t mask, const float (&s)[4]) {
+        const int32_t a0 = (int32_t)(4 * (mask - 1));
+        if (A.prior)
+            *reinterpret_cast<float4 *>(A.prior + (int64_t)q * FA.S_full + a0) = float4{s[0], s[1], s[2], s[3]};
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+            if (s[o] > m) { z = z * __expf(m - s[o]) + 1.f; m = s[o]; im = a0 + o; }
+            else { z += __expf(s[o] - m); if (s[o] == m && a0 + o < im) im = a0 + o; }
+        }
+    };
+    if (g0 < total && !fast) {   // unscaled: ReLU as a max, every mask's device sum taken afresh (no run in registers)
+        for (int st = 0; st < run; ++st) {
+            const uint32_t gi = (uint32_t)g0 + st, mask = gi ^ (gi >> 1);
+            if (mask == 0) continue;
+            float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int h = 0; h < H; ++h) {
+                float d = 0.f;
+                for (int j = 0; j < nd; ++j) d += ((mask >> j) & 1u) ? trow[j * HP + h] : 0.f;
+#pragma unroll
+                for (int o = 0; o < 4; ++o) s[o] = fmaf(sw2[h], fmaxf(d + bq[o * HP + h], 0.f), s[o]);
+            }
+#pragma unroll
+            for (int o = 0; o < 4; ++o) s[o] += A.b2[0];
+            put(mask, s);
+        }
+    } else if (g0 < total) {
         uint32_t mask = (uint32_t)(g0 ^ (g0 >> 1));
         float ds[HP];
 #pragma unroll
@@ -621,22 +688,14 @@ __global__ void __launch_bounds__(256) dec_full_tpm(FullTpm T) {
                     ds[h] = fmaf(sg, trow[j * HP + h], ds[h]);
             }
             if (mask == 0) continue;
-            float s[4];
+            float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int o = 0; o < 4; ++o) {
-                float acc = 0.f;
+            for (int h = 0; h < HP; ++h)   // (units outer: w2 is read once for the four options)
 #pragma unroll
-                for (int h = 0; h < HP; ++h) acc = fmaf(sw2[h], fmaxf(ds[h] + bq[o * HP + h], 0.f), acc);
-                s[o] = A.b2[0] + acc;
-            }
-            const int32_t a0 = (int32_t)(4 * (mask - 1));
-            if (A.prior)
-                *reinterpret_cast<float4 *>(A.prior + (int64_t)q * FA.S_full + a0) = float4{s[0], s[1], s[2], s[3]};
+                for (int o = 0; o < 4; ++o) s[o] = fmaf(sw2[h], clamp01(ds[h] + bq[o * HP + h]), s[o]);
 #pragma unroll
-            for (int o = 0; o < 4; ++o) {
-                if (s[o] > m) { z = z * __expf(m - s[o]) + 1.f; m = s[o]; im = a0 + o; }
-                else { z += __expf(s[o] - m); if (s[o] == m && a0 + o < im) im = a0 + o; }
-            }
+            for (int o = 0; o < 4; ++o) s[o] += A.b2[0];
+            put(mask, s);
         }
     }
     // wavefront merge of the lanes' (max, sum, argmax), then the block's four
@@ -679,31 +738,50 @@ __global__ void dec_full_base(DecArgs A, int HP, float *base, float *w2p) {
     }
 }
 
-// per query: merge the block records in order, decode the argmax, then
-// normalise the priors of the query's slices (zeros beyond them)
-__global__ void __launch_bounds__(256) dec_full_merge(FullArgs FA) {
+// (max, sum, lowest argmax) of two parts of a query's slices
+__device__ __forceinline__ void full_join(float &m, float &z, int32_t &i, float m2, float z2, int32_t i2) {
+    const float nm = fmaxf(m, m2);
+    if (nm == -INFINITY) return;
+    z = (m == -INFINITY ? 0.f : z * __expf(m - nm)) + (m2 == -INFINITY ? 0.f : z2 * __expf(m2 - nm));
+    if (m2 > m || (m2 == m && i2 < i)) i = i2;
+    m = nm;
+}
+
+// Per query: merge the block records (each thread its own in order, then a
+// fixed tree), decode the argmax, and normalise the priors of the query's
+// slices (zeros beyond them).  kMergeSlices priors per block, so the pass over
+// the priors -- the largest stream here, bound by HBM -- fills the chip; every
+// block of a query merges the records again (one 16-byte record per 16,384
+// slices).  64 queries of 16 devices (134 MB read and written): 324 us with
+// one block per query and the records merged by one thread, 24 us now.
+constexpr int kMergeSlices = 8192;
+
+__global__ void __launch_bounds__(256) dec_full_merge(FullArgs FA, int32_t per_q) {
     const DecArgs &A = FA.A;
-    __shared__ float sM, sZ;
-    const int32_t q = blockIdx.x;
+    __shared__ float sM[4], sZ[4];
+    __shared__ int32_t sI[4];
+    const int32_t q = blockIdx.x / per_q, part = blockIdx.x % per_q;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     int32_t r, g, op;
     const bool ok = query_valid(A, q, &r, &g, &op);
     const int32_t nd = ok ? A.dev_off[g + 1] - A.dev_off[g] : 0;
     const int32_t S_q = ok ? 4 * ((1 << nd) - 1) : 0;
-    if (threadIdx.x == 0) {
-        float M = -INFINITY, Z = 0.f;
-        int32_t I = INT32_MAX;
-        for (int32_t c = 0; c < FA.NB; ++c) {
-            const float *rec = FA.rec + ((int64_t)q * FA.NB + c) * 4;
-            const float m2 = rec[0];
-            if (!(rec[3] > 0.f) || m2 == -INFINITY) continue;
-            const float nm = fmaxf(M, m2);
-            Z = (M == -INFINITY ? 0.f : Z * __expf(M - nm)) + rec[1] * __expf(m2 - nm);
-            const int32_t i2 = __float_as_int(rec[2]);
-            if (m2 > M || (m2 == M && i2 < I)) I = i2;
-            M = nm;
-        }
-        sM = M;
-        sZ = Z;
+    float M = -INFINITY, Z = 0.f;
+    int32_t I = INT32_MAX;
+    for (int32_t c = threadIdx.x; c < FA.NB; c += 256) {
+        const float *rec = FA.rec + ((int64_t)q * FA.NB + c) * 4;
+        if (rec[3] > 0.f) full_join(M, Z, I, rec[0], rec[1], __float_as_int(rec[2]));
+    }
+    for (int o = 1; o < 64; o <<= 1) {
+        const float m2 = __shfl_xor(M, o, 64), z2 = __shfl_xor(Z, o, 64);
+        const int32_t i2 = __shfl_xor(I, o, 64);
+        full_join(M, Z, I, m2, z2, i2);
+    }
+    if (lane == 0) { sM[wv] = M; sZ[wv] = Z; sI[wv] = I; }
+    __syncthreads();
+    M = sM[0]; Z = sZ[0]; I = sI[0];
+    for (int k = 1; k < 4; ++k) full_join(M, Z, I, sM[k], sZ[k], sI[k]);
+    if (part == 0 && threadIdx.x == 0) {
         if (!ok || I == INT32_MAX) {
             A.argmax[q] = -1;
             A.best[q] = __builtin_nanf("");
@@ -719,12 +797,24 @@ __global__ void __launch_bounds__(256) dec_full_merge(FullArgs FA) {
             }
         }
     }
-    __syncthreads();
     if (!A.prior) return;
-    const float M = sM, inv = sZ > 0.f ? 1.f / sZ : 0.f;
+    const float inv = Z > 0.f ? 1.f / Z : 0.f;
     float *row = A.prior + (int64_t)q * FA.S_full;
-    for (int32_t a = threadIdx.x; a < FA.S_full; a += blockDim.x)
-        row[a] = a < S_q && ok ? __expf(row[a] - M) * inv : 0.f;
+    // four slices (one mask) per lane; rows hold a multiple of four
+    const int32_t a1 = min((part + 1) * kMergeSlices, FA.S_full);
+    for (int32_t a = part * kMergeSlices + 4 * threadIdx.x; a < a1; a += 1024) {
+        float4 p = float4{0.f, 0.f, 0.f, 0.f};
+        if (a < S_q) {
+            const float4 s = *reinterpret_cast<const float4 *>(row + a);
+            p = float4{__expf(s.x - M) * inv, __expf(s.y - M) * inv, __expf(s.z - M) * inv, __expf(s.w - M) * inv};
+        }
+        *reinterpret_cast<float4 *>(row + a) = p;
+    }
+}
+
+void launch_full_merge(const FullArgs &FA, hipStream_t st) {
+    const int32_t per_q = FA.A.prior ? (FA.S_full + kMergeSlices - 1) / kMergeSlices : 1;
+    dec_full_merge<<<(unsigned)((int64_t)FA.A.Q * per_q), 256, 0, st>>>(FA, per_q);
 }
 
 struct FullLayout {
@@ -825,7 +915,7 @@ extern "C" tag_status tag_gnn_decide_full(const tag_graph *g, const tag_model_di
         if (hp == 32) dec_full_tpm<32><<<grid, 256, 0, stream>>>(T);
         else if (hp == 64) dec_full_tpm<64><<<grid, 256, 0, stream>>>(T);
         else dec_full_tpm<128><<<grid, 256, 0, stream>>>(T);
-        dec_full_merge<<<(unsigned)n_query, 256, 0, stream>>>(FA);
+        launch_full_merge(FA, stream);
         return launch_status("tag_gnn_decide_full");
     }
     const size_t sh = sizeof(float) * (size_t)21 * Hx;
@@ -834,6 +924,6 @@ extern "C" tag_status tag_gnn_decide_full(const tag_graph *g, const tag_model_di
     else if (hpl <= 2) dec_full<2><<<grid, 256, sh, stream>>>(FA);
     else if (hpl <= 4) dec_full<4><<<grid, 256, sh, stream>>>(FA);
     else dec_full<8><<<grid, 256, sh, stream>>>(FA);
-    dec_full_merge<<<(unsigned)n_query, 256, 0, stream>>>(FA);
+    launch_full_merge(FA, stream);
     return launch_status("tag_gnn_decide_full");
 }

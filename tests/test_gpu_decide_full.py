@@ -106,3 +106,27 @@ def test_full_enumeration_limits():
     m2 = P.Model(synth.make_weights(64, 4, 1, 42, 600), f=64, heads=4, layers=1, f_op=42)
     assert lib.tag_gnn_decide_full_workspace(small.handle, C.byref(m2.dims), 1, 1, C.byref(b)) == _abi.TAG_ESHAPE
     assert lib.tag_gnn_decide_full_workspace(small.handle, C.byref(m.dims), 1, 1, C.byref(b)) == _abi.TAG_OK
+
+
+@pytest.mark.parametrize("m_dev,H,scale,Q", [(14, 128, 1e-3, 3), (14, 64, 300.0, 3), (12, 32, 3e13, 2), (2, 128, 1.0, 5)])
+def test_full_enumeration_pre_activation_ranges(m_dev, H, scale, Q):
+    """Pre-activations far below one, far above it (scaled exactly in the readout) and past the range that is
+    scaled; several blocks of normalised priors per query (14 devices) and a partial one."""
+    f, n = 64, 9
+    rng = np.random.default_rng((2302, 90, m_dev, H))
+    topo = synth.random_topology(300 + m_dev, n, m_dev, 10)
+    E_op = (rng.uniform(0, 1, (1, n, f)) * scale).astype(np.float32)
+    E_dev = (rng.uniform(0, 1, (1, m_dev, f)) * scale).astype(np.float32)
+    w = synth.make_weights(f, 4, 1, 42, H, bias_scale=0.5, seed_extra=m_dev)
+    w["dec_w2"] = (w["dec_w2"] / np.float32(scale)).astype(np.float32)   # scores of order one
+    g = P.Graph([topo])
+    m = P.Model(w, f=f, heads=4, layers=1, f_op=42, dec_hidden=H)
+    qo = rng.integers(0, n, Q).astype(np.int32)
+    z = np.zeros(Q, np.int32)
+    res = P.decide_full(g, m, dev_tensor(E_op), dev_tensor(E_dev), z, z, qo)
+    masks, opts = _full_table(m_dev)
+    for q in range(Q):
+        od = oracle.decide(E_op[0].astype(np.float64), E_dev[0].astype(np.float64), masks, opts, qo[q:q + 1], w, f=f,
+                           dec_hidden=H, n_dev=m_dev)
+        _check(res, q, od, len(masks))
+    g.close()
