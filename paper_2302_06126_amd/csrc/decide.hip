@@ -30,12 +30,13 @@ struct DecArgs {
     const float *P;      // projection rows [Hx][2F+4] (W1, or w2 for the linear head)
     const float *b1, *w2, *b2;
     const int32_t *q_rep, *q_graph, *q_op;
-    float *t;            // [R*n_dev][Hx]
+    float *t;            // [R*n_dev][Hx]; dead once u is formed (see bound)
     float *u;            // [R*G][Hx][S]
     float *v;            // [Q][Hx]
     int32_t *argmax;
     float *best, *prior;
     tag_decision *dec;
+    int32_t bound;       // dec_slice leaves max_a |u[rg][h][a]| in t's row of rg's first device
 };
 
 // u[rg][h][a] = sum_{j in mask_a} t[dev(rg, j)][h] + P[h][2F + opt_a] (+ b1[h])
@@ -62,6 +63,9 @@ __global__ void __launch_bounds__(256) dec_slice(DecArgs A) {
     }
     __syncthreads();
     const uint64_t keep = nd >= 64 ? ~0ull : ((1ull << nd) - 1ull);
+    int ub[kSliceH];   // bits of the largest |u| (as integers a NaN is the largest)
+#pragma unroll
+    for (int hh = 0; hh < kSliceH; ++hh) ub[hh] = 0;
     for (int32_t a = threadIdx.x; a < A.S; a += blockDim.x) {
         uint64_t m = A.mask[a] & keep;
         const int opt = min((int)A.option[a], 3);
@@ -78,6 +82,27 @@ __global__ void __launch_bounds__(256) dec_slice(DecArgs A) {
 #pragma unroll
         for (int hh = 0; hh < kSliceH; ++hh)
             if (h0 + hh < A.Hx) u[(int64_t)hh * A.S] = acc[hh];
+#pragma unroll
+        for (int hh = 0; hh < kSliceH; ++hh) ub[hh] = max(ub[hh], __float_as_int(fabsf(acc[hh])));
+    }
+    if (A.bound) {   // this block alone reads these eight columns of the graph's t rows
+        // maxima of the eight units over the wavefront: each exchange halves the
+        // units a lane holds, so lane l ends with unit 4 l0 + 2 l1 + l2 (its low bits)
+        __shared__ int bl[4][kSliceH];
+        const int l0 = threadIdx.x & 1, l1 = (threadIdx.x >> 1) & 1, l2 = (threadIdx.x >> 2) & 1;
+        int v4[4], v2[2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v4[i] = max(l0 ? ub[4 + i] : ub[i], __shfl_xor(l0 ? ub[i] : ub[4 + i], 1, 64));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) v2[i] = max(l1 ? v4[2 + i] : v4[i], __shfl_xor(l1 ? v4[i] : v4[2 + i], 2, 64));
+        int b = max(l2 ? v2[1] : v2[0], __shfl_xor(l2 ? v2[0] : v2[1], 4, 64));
+        for (int o = 8; o < 64; o <<= 1) b = max(b, __shfl_xor(b, o, 64));
+        if ((threadIdx.x & 63) < kSliceH) bl[threadIdx.x >> 6][4 * l0 + 2 * l1 + l2] = b;
+        __syncthreads();
+        const int hh = threadIdx.x;
+        if (hh < kSliceH && h0 + hh < A.Hx)
+            A.t[((int64_t)r * A.n_dev + d0) * A.Hx + h0 + hh] =
+                __int_as_float(max(max(bl[0][hh], bl[1][hh]), max(bl[2][hh], bl[3][hh])));
     }
 }
 
@@ -99,6 +124,20 @@ __global__ void dec_query_rows(DecArgs A, int32_t *qrow) {
 // instruction that makes x
 __device__ __forceinline__ float clamp01(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, 1.f); }
 
+// The exponent e >= 0 that brings values of magnitude <= b (finite), and the
+// rounding of their sums, into [-1, 1] when they are scaled by 2^-e.
+__device__ __forceinline__ int relu_exponent(float b) {
+    int e = 0;
+    frexpf(b, &e);
+    return max(e + 1, 0);
+}
+// whether a unit with pre-activations of magnitude <= b and readout weight w
+// may be scaled so: false for infinities, NaN and sizes where 2^-e b or 2^e w
+// would leave the normal range
+__device__ __forceinline__ bool relu_scalable(float b, float w) {
+    return b < 0x1p40f && fabsf(w) < 0x1p80f;
+}
+
 constexpr int kScoreThreads = 256;
 
 __device__ __forceinline__ float slice_score(const DecArgs &A, const float *urg, const float *vq,
@@ -116,6 +155,26 @@ __device__ __forceinline__ float slice_score(const DecArgs &A, const float *urg,
     }
     for (; h < A.H; ++h) s = fmaf(w2s[h], fmaxf(urg[(int64_t)h * A.S + a] + vq[h], 0.f), s);
     return A.b2[0] + s;
+}
+
+// argmax, best score and decoded decision of query q (topology g)
+__device__ void write_decision(const DecArgs &A, int32_t q, int32_t g, float M, int32_t best) {
+    if (best < 0 || best >= A.S) {   // no comparable score (NaN inputs)
+        A.argmax[q] = -1;
+        A.best[q] = __builtin_nanf("");
+        if (A.dec) A.dec[q] = tag_decision{0, 0, 0, 0, 0};
+        return;
+    }
+    A.argmax[q] = best;
+    A.best[q] = M;
+    if (A.dec) {
+        const int32_t nd = A.dev_off[g + 1] - A.dev_off[g];
+        const uint64_t valid = nd >= 64 ? ~0ull : ((1ull << nd) - 1ull);
+        const uint64_t msk = A.mask[best] & valid;
+        const int o = min((int)A.option[best], 3);
+        const int pc = __popcll(msk);
+        A.dec[q] = tag_decision{msk, o, o == 3 ? 1 : pc, o == 0 ? 0 : (o == 1 ? 1 : 2), o == 2 ? 1 : 0};
+    }
 }
 
 // Max (lowest index on ties) and sum of exponentials over the block's
@@ -147,24 +206,7 @@ __device__ void finish_query(const DecArgs &A, int32_t q, int32_t g, float m, in
             A.prior[(int64_t)q * A.S + a] = __expf(s - M) * inv;
         }
     }
-    if (threadIdx.x == 0) {
-        if (best < 0 || best >= A.S) {   // no comparable score (NaN inputs)
-            A.argmax[q] = -1;
-            A.best[q] = __builtin_nanf("");
-            if (A.dec) A.dec[q] = tag_decision{0, 0, 0, 0, 0};
-            return;
-        }
-        A.argmax[q] = best;
-        A.best[q] = M;
-        if (A.dec) {
-            const int32_t nd = A.dev_off[g + 1] - A.dev_off[g];
-            const uint64_t valid = nd >= 64 ? ~0ull : ((1ull << nd) - 1ull);
-            const uint64_t msk = A.mask[best] & valid;
-            const int o = min((int)A.option[best], 3);
-            const int pc = __popcll(msk);
-            A.dec[q] = tag_decision{msk, o, o == 3 ? 1 : pc, o == 0 ? 0 : (o == 1 ? 1 : 2), o == 2 ? 1 : 0};
-        }
-    }
+    if (threadIdx.x == 0) write_decision(A, q, g, M, best);
 }
 
 __device__ void invalid_query(const DecArgs &A, int32_t q) {
@@ -175,6 +217,33 @@ __device__ void invalid_query(const DecArgs &A, int32_t q) {
     }
     if (A.prior)
         for (int32_t a = threadIdx.x; a < A.S; a += blockDim.x) A.prior[(int64_t)q * A.S + a] = 0.f;
+}
+
+// queries q0 .. q0 + nq - 1 one by one (256 threads)
+__device__ void score_singly(const DecArgs &A, int32_t q0, int32_t nq, float *vq, const float *w2s, float *red_m,
+                             int32_t *red_i, float *red_z) {
+    for (int i = 0; i < nq; ++i) {
+        const int32_t q = q0 + i;
+        int32_t r, g, op;
+        if (!query_valid(A, q, &r, &g, &op)) {
+            invalid_query(A, q);
+            continue;
+        }
+        __syncthreads();   // the previous query's reads of v are done
+        for (int h = threadIdx.x; h < A.Hx; h += blockDim.x) vq[h] = A.v[(int64_t)q * A.Hx + h];
+        __syncthreads();
+        const float *urg = A.u + ((int64_t)r * A.G + g) * A.Hx * A.S;
+        // max (lowest index on ties) and the running sum of exponentials
+        float m = -INFINITY, z = 0.f;
+        int32_t im = INT32_MAX;
+        for (int32_t a = threadIdx.x; a < A.S; a += blockDim.x) {
+            float s = slice_score(A, urg, vq, w2s, a);
+            if (A.prior) A.prior[(int64_t)q * A.S + a] = s;
+            if (s > m) { z = z * __expf(m - s) + 1.f; m = s; im = a; }
+            else z += __expf(s - m);
+        }
+        finish_query(A, q, g, m, im, z, red_m, red_i, red_z);
+    }
 }
 
 // QB consecutive queries per block: scores, softmax prior, argmax, decoded
@@ -248,28 +317,138 @@ __global__ void __launch_bounds__(kScoreThreads) dec_score(DecArgs A) {
         for (int i = 0; i < QB; ++i) finish_query(A, q0 + i, gq[0], m[i], im[i], z[i], red_m, red_i, red_z);
         return;
     }
-    for (int i = 0; i < nq; ++i) {
-        const int32_t q = q0 + i;
-        int32_t r, g, op;
-        if (!query_valid(A, q, &r, &g, &op)) {
-            invalid_query(A, q);
-            continue;
+    score_singly(A, q0, nq, sh, w2s, red_m, red_i, red_z);
+}
+
+// kGroupQ consecutive queries per block, two slices and half of the hidden
+// units per thread: for calls with many queries per candidate (a whole op group of each), where
+// re-reading u from L2 for every query and the vector pipe bound the readout.
+// The block's queries must read one candidate's u (else they go one by one, in
+// the way of dec_score).  Hidden unit h of the block is scaled by a
+// power of two that brings its pre-activations into [-1, 1] (bound: max |u|
+// left by dec_slice plus max |v|), its readout weight by the inverse, both
+// exactly, so the ReLU is the clamp of one multiply-add and a (slice, query,
+// unit) costs two instructions, with the same bits; v and the weights are LDS
+// broadcasts, shared by the thread's two slices.  Scores meet in LDS, and each
+// wavefront finishes half of the queries.  42,496 queries, 256 slices, H = 256:
+// dec_score<4> 346 us (add, max, multiply-add; 2.8 GB of u reads from L2), this 240 us
+// plus 4 us in dec_slice for the bounds (vector issue: 162 us).
+constexpr int kGroupQ = 8;
+constexpr int kGroupMinQ = 8192;                     // blocks to fill the chip (1,024 of them)
+constexpr int kGroupMaxH = 512, kGroupMaxS = 512;    // 20 + 16 KiB of LDS: four blocks per CU
+
+__global__ void __launch_bounds__(kScoreThreads) dec_score_group(DecArgs A) {
+    extern __shared__ __attribute__((aligned(16))) float sh[];   // v [H][8] | (2^-e, 2^e w2) [H][2] | scores [8][S]
+    __shared__ float red_m[kScoreThreads], red_z[kScoreThreads];
+    __shared__ int32_t red_i[kScoreThreads];
+    const int32_t q0 = (int32_t)xcd_swizzle(blockIdx.x, gridDim.x) * kGroupQ;
+    const int32_t nq = min(kGroupQ, A.Q - q0);
+    const int H = A.H;
+    int32_t r0 = 0, g0 = 0, op;
+    bool shared = query_valid(A, q0, &r0, &g0, &op);
+    for (int i = 1; i < nq; ++i) {
+        int32_t r, g;
+        shared = query_valid(A, q0 + i, &r, &g, &op) && shared && r == r0 && g == g0;
+    }
+    float *sv = sh, *sc = sh + kGroupQ * H, *ss = sc + 2 * H;
+    bool ok = true;
+    if (shared) {
+        const float *ub = A.t + ((int64_t)r0 * A.n_dev + A.dev_off[g0]) * A.Hx;
+        for (int h = threadIdx.x; h < H; h += kScoreThreads) {
+            float v[kGroupQ], b = ub[h], vm = 0.f;
+#pragma unroll
+            for (int i = 0; i < kGroupQ; ++i) {   // (a last group short of queries repeats its last one)
+                v[i] = A.v[(int64_t)(q0 + min(i, nq - 1)) * A.Hx + h];
+                vm += fabsf(v[i]);
+            }
+            const float w2 = A.w2[h];
+            b += vm;
+            ok = ok && relu_scalable(b, w2);
+            const int e = relu_exponent(b);
+#pragma unroll
+            for (int i = 0; i < kGroupQ; ++i) sv[h * kGroupQ + i] = ldexpf(v[i], -e);
+            sc[2 * h] = ldexpf(1.f, -e);
+            sc[2 * h + 1] = ldexpf(w2, e);
         }
-        float *vq = sh;
-        __syncthreads();   // the previous query's reads of v are done
-        for (int h = threadIdx.x; h < A.Hx; h += blockDim.x) vq[h] = A.v[(int64_t)q * A.Hx + h];
+    }
+    if (!__syncthreads_and(ok && shared)) {
         __syncthreads();
-        const float *urg = A.u + ((int64_t)r * A.G + g) * A.Hx * A.S;
-        // max (lowest index on ties) and the running sum of exponentials
-        float m = -INFINITY, z = 0.f;
-        int32_t im = INT32_MAX;
-        for (int32_t a = threadIdx.x; a < A.S; a += blockDim.x) {
-            float s = slice_score(A, urg, vq, w2s, a);
-            if (A.prior) A.prior[(int64_t)q * A.S + a] = s;
-            if (s > m) { z = z * __expf(m - s) + 1.f; m = s; im = a; }
-            else z += __expf(s - m);
+        float *w2s = sh + A.Hx;
+        for (int h = threadIdx.x; h < H; h += kScoreThreads) w2s[h] = A.w2[h];
+        score_singly(A, q0, nq, sh, w2s, red_m, red_i, red_z);
+        return;
+    }
+    const float *urg = A.u + ((int64_t)r0 * A.G + g0) * A.Hx * A.S;
+    const float b2 = A.b2[0];
+    const int S = A.S;
+    const int half = threadIdx.x >> 7, hb = half ? H / 2 : 0, he = half ? H : H / 2;
+    for (int32_t a0 = 0; a0 < S; a0 += kScoreThreads) {
+        const int32_t a = a0 + (threadIdx.x & 127);
+        const float *ua = urg + min(a, S - 1), *uc = urg + min(a + 128, S - 1);
+        float s[2][kGroupQ];
+#pragma unroll
+        for (int i = 0; i < kGroupQ; ++i) s[0][i] = s[1][i] = 0.f;
+        auto unit = [&](int h, float u0, float u1) {
+            const float2 c = *reinterpret_cast<const float2 *>(sc + 2 * h);
+            const float4 va = *reinterpret_cast<const float4 *>(sv + h * kGroupQ);
+            const float4 vb = *reinterpret_cast<const float4 *>(sv + h * kGroupQ + 4);
+            const float v[kGroupQ] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
+#pragma unroll
+            for (int i = 0; i < kGroupQ; ++i) {
+                s[0][i] = fmaf(c.y, clamp01(fmaf(u0, c.x, v[i])), s[0][i]);
+                s[1][i] = fmaf(c.y, clamp01(fmaf(u1, c.x, v[i])), s[1][i]);
+            }
+        };
+        int h = hb;
+        for (; h + 8 <= he; h += 8) {
+            float u0[8], u1[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { u0[k] = ua[(int64_t)(h + k) * S]; u1[k] = uc[(int64_t)(h + k) * S]; }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) unit(h + k, u0[k], u1[k]);
         }
-        finish_query(A, q, g, m, im, z, red_m, red_i, red_z);
+        for (; h < he; ++h) unit(h, ua[(int64_t)h * S], uc[(int64_t)h * S]);
+        if (half) {
+#pragma unroll
+            for (int i = 0; i < kGroupQ; ++i) {
+                if (a < S) ss[i * S + a] = s[0][i];
+                if (a + 128 < S) ss[i * S + a + 128] = s[1][i];
+            }
+        }
+        __syncthreads();
+        if (!half) {
+#pragma unroll
+            for (int i = 0; i < kGroupQ; ++i) {
+                if (a < S) ss[i * S + a] += s[0][i] + b2;
+                if (a + 128 < S) ss[i * S + a + 128] += s[1][i] + b2;
+            }
+        }
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    for (int i = threadIdx.x >> 6; i < nq; i += kScoreThreads / 64) {
+        const int32_t q = q0 + i;
+        float m = -INFINITY;
+        int32_t im = INT32_MAX;
+        for (int32_t a = lane; a < S; a += 64)
+            if (ss[i * S + a] > m) { m = ss[i * S + a]; im = a; }
+        for (int o = 1; o < 64; o <<= 1) {
+            const float m2 = __shfl_xor(m, o, 64);
+            const int32_t i2 = __shfl_xor(im, o, 64);
+            if (m2 > m || (m2 == m && i2 < im)) { m = m2; im = i2; }
+        }
+        float z = 0.f;
+        for (int32_t a = lane; a < S; a += 64) {
+            const float x = __expf(ss[i * S + a] - m);
+            ss[i * S + a] = x;
+            z += x;
+        }
+        for (int o = 1; o < 64; o <<= 1) z += __shfl_xor(z, o, 64);
+        if (A.prior) {
+            const float inv = 1.f / z;
+            for (int32_t a = lane; a < S; a += 64) A.prior[(int64_t)q * S + a] = ss[i * S + a] * inv;
+        }
+        if (lane == 0) write_decision(A, q, g0, m, im);
     }
 }
 
@@ -363,6 +542,8 @@ tag_status decide_run(const tag_graph *g, const tag_model_dims *dims, const tag_
     A.t = L.t; A.u = L.u; A.v = L.v;
     A.argmax = argmax; A.best = best_score; A.prior = prior; A.dec = decision;
     const int din = 2 * A.F + 4;
+    const bool group = A.Q >= kGroupMinQ && H > 0 && H <= kGroupMaxH && A.S <= kGroupMaxS;
+    A.bound = group ? 1 : 0;
     prof_begin(TAG_STAGE_DECIDE, stream);
     // t = E_dev W1_dev^T and v = E_op[query rows] W1_op^T as MFMA GEMMs
     launch_small_gemm(SmallGemm{E_dev, A.F, (int64_t)A.R * A.n_dev, nullptr, A.F, A.P, din, Hx, nullptr, 0,
@@ -370,8 +551,11 @@ tag_status decide_run(const tag_graph *g, const tag_model_dims *dims, const tag_
     dec_query_rows<<<grid_for(A.Q), 256, 0, stream>>>(A, L.qrow);
     launch_small_gemm(SmallGemm{E_op, A.F, A.Q, L.qrow, A.F, A.P + A.F, din, Hx, nullptr, 0, A.v, Hx, 0}, stream);
     dec_slice<<<(unsigned)((int64_t)A.R * A.G * ((Hx + kSliceH - 1) / kSliceH)), 256, 0, stream>>>(A);
-    // four queries per block once there are enough blocks to fill the GPU
-    if (A.Q >= 8192)
+    // eight or four queries per block once there are enough blocks to fill the GPU
+    if (group)
+        dec_score_group<<<(unsigned)((A.Q + kGroupQ - 1) / kGroupQ), kScoreThreads,
+                          sizeof(float) * ((kGroupQ + 2) * Hx + kGroupQ * A.S), stream>>>(A);
+    else if (A.Q >= 8192)
         dec_score<4><<<(unsigned)((A.Q + 3) / 4), kScoreThreads, sizeof(float) * (4 * Hx + H), stream>>>(A);
     else
         dec_score<1><<<(unsigned)A.Q, kScoreThreads, sizeof(float) * (Hx + H), stream>>>(A);
@@ -561,20 +745,6 @@ __global__ void __launch_bounds__(256) dec_full(FullArgs FA) {
 // their runs, every step toggles the same device j = ctz(step) in all
 // lanes; the t row of j, the option bases and w2 are wave-uniform LDS reads.
 constexpr int kFullRun = 16;
-
-// The exponent e >= 0 that brings values of magnitude <= b (finite), and the
-// rounding of their sums, into [-1, 1] when they are scaled by 2^-e.
-__device__ __forceinline__ int relu_exponent(float b) {
-    int e = 0;
-    frexpf(b, &e);
-    return max(e + 1, 0);
-}
-// whether a unit with pre-activations of magnitude <= b and readout weight w
-// may be scaled so: false for infinities, NaN and sizes where 2^-e b or 2^e w
-// would leave the normal range
-__device__ __forceinline__ bool relu_scalable(float b, float w) {
-    return b < 0x1p40f && fabsf(w) < 0x1p80f;
-}
 
 struct FullTpm {
     FullArgs FA;

@@ -410,3 +410,32 @@ def test_decide_invalid_queries_and_high_mask_bits():
     ok = res["argmax"] >= 0
     assert np.array_equal(res["best"][ok], res2["best"][ok])
     assert np.array_equal(res2["mask"][ok], masks[res["argmax"][ok]])
+
+
+@pytest.mark.parametrize("m_dev,f,H,S,scale", [(5, 64, 37, 61, 1.0), (64, 64, 512, 512, 30.0), (9, 128, 1, 129, 1.0),
+                                               (9, 64, 130, 257, 1e13), (9, 64, 64, 513, 1.0)])
+def test_decide_query_groups(m_dev, f, H, S, scale):
+    """8,195 queries in groups of eight: odd widths and tables, the largest table of the group kernel and one past it,
+    groups that straddle candidates, a short last group, and pre-activations past the range that is scaled."""
+    topo, R, E_op, E_dev, w, masks, opts = _decide_case(m_dev, f, H, S, m_dev + H + 7)
+    E_op, E_dev = E_op * np.float32(scale), E_dev * np.float32(scale)
+    w["dec_w2"] = (w["dec_w2"] / np.float32(scale)).astype(np.float32)
+    g = P.Graph([topo])
+    m = P.Model(w, f=f, heads=4, layers=1, f_op=42, dec_hidden=H)
+    rng = np.random.default_rng((m_dev, H))
+    Q = 8195
+    qr = np.sort(rng.integers(0, R, Q)).astype(np.int32)
+    qo = rng.integers(0, topo.n_op, Q).astype(np.int32)
+    qo[100] = topo.n_op
+    res = P.decide(g, m, dev_tensor(E_op), dev_tensor(E_dev), masks, opts, qr, np.zeros(Q, np.int32), qo)
+    assert res["argmax"][100] == -1
+    edges = np.flatnonzero(np.diff(qr)) + 1
+    for q in np.unique(np.concatenate([edges - 1, edges, [0, 99, 101, 8191, 8192, Q - 1], rng.choice(Q, 40)])):
+        if q == 100:
+            continue
+        od = oracle.decide(E_op[qr[q]].astype(np.float64), E_dev[qr[q]].astype(np.float64), masks, opts,
+                           qo[q:q + 1], w, f=f, dec_hidden=H, n_dev=m_dev)
+        if decide_gap_ok(od["prior"][0], od["best"][0], 1e-5):
+            assert res["argmax"][q] == od["argmax"][0], q
+        np.testing.assert_allclose(res["best"][q], od["best"][0], rtol=1e-5, atol=1e-5)
+        np.testing.assert_allclose(res["prior"][q], od["prior"][0], rtol=1e-4, atol=1e-7)
