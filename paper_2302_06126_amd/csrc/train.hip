@@ -48,93 +48,11 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- GEMM
-// C_z (+)= sum_{k in split z} A(m, k) B(k, n) on MFMA 16x16x4 (fp32).
-// A(m, k) = A[m lda + k] (a_kc) or A[k lda + m]; B(k, n) = B[n ldb + k]
-// (b_kc) or B[k ldb + n].  Column ones_col of an n-contiguous B reads 1
-// (it turns the product into column sums of A).  64 x 64 block tiles of
-// four 32 x 32 wavefront tiles, k-chunks of 16 staged through LDS with the
-// next chunk's loads in flight.
-struct Gemm {
-    const float *A;
-    int64_t lda;
-    const float *B;
-    int64_t ldb;
-    int64_t M, N, K;
-    int64_t ones_col;
-    float *C;
-    int64_t ldc, c_split;
-    int64_t k_per;
-    int accumulate;
-};
-
-constexpr int GM = 64, GN = 64, GK = 16;
-
-template <bool AKC, bool BKC>
-__global__ void __launch_bounds__(256) gemm_f32(Gemm G) {
-    __shared__ float As[GK][GM + 4];
-    __shared__ float Bs[GK][GN + 4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int64_t m0 = (int64_t)blockIdx.x * GM, n0 = (int64_t)blockIdx.y * GN;
-    const int64_t kb = (int64_t)blockIdx.z * G.k_per, ke = std::min<int64_t>(G.K, kb + G.k_per);
-    f4 acc[2][2];
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-    float ra[4], rb[4];
-    auto gload = [&](int64_t k0) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (AKC) {
-                const int64_t m = m0 + (tid >> 4) + 16 * q, k = k0 + (tid & 15);
-                ra[q] = (m < G.M && k < ke) ? G.A[m * G.lda + k] : 0.f;
-            } else {
-                const int64_t m = m0 + (tid & 63), k = k0 + (tid >> 6) + 4 * q;
-                ra[q] = (m < G.M && k < ke) ? G.A[k * G.lda + m] : 0.f;
-            }
-            if (BKC) {
-                const int64_t n = n0 + (tid >> 4) + 16 * q, k = k0 + (tid & 15);
-                rb[q] = (n < G.N && k < ke) ? G.B[n * G.ldb + k] : 0.f;
-            } else {
-                const int64_t n = n0 + (tid & 63), k = k0 + (tid >> 6) + 4 * q;
-                rb[q] = (k < ke && n < G.N) ? (n == G.ones_col ? 1.f : G.B[k * G.ldb + n]) : 0.f;
-            }
-        }
-    };
-    if (kb < ke) gload(kb);
-    for (int64_t k0 = kb; k0 < ke; k0 += GK) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (AKC) As[tid & 15][(tid >> 4) + 16 * q] = ra[q];
-            else As[(tid >> 6) + 4 * q][tid & 63] = ra[q];
-            if (BKC) Bs[tid & 15][(tid >> 4) + 16 * q] = rb[q];
-            else Bs[(tid >> 6) + 4 * q][tid & 63] = rb[q];
-        }
-        __syncthreads();
-        if (k0 + GK < ke) gload(k0 + GK);
-#pragma unroll
-        for (int kk = 0; kk < GK; kk += 4) {
-            float a[2], b[2];
-            for (int i = 0; i < 2; ++i) a[i] = As[kk + (lane >> 4)][wm * 32 + i * 16 + (lane & 15)];
-            for (int j = 0; j < 2; ++j) b[j] = Bs[kk + (lane >> 4)][wn * 32 + j * 16 + (lane & 15)];
-            for (int i = 0; i < 2; ++i)
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    float *C = G.C + (int64_t)blockIdx.z * G.c_split;
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) {
-            const int64_t n = n0 + wn * 32 + j * 16 + (lane & 15);
-            if (n >= G.N) continue;
-            for (int v = 0; v < 4; ++v) {
-                const int64_t m = m0 + wm * 32 + i * 16 + 4 * (lane >> 4) + v;
-                if (m >= G.M) continue;
-                float *p = C + m * G.ldc + n;
-                *p = G.accumulate ? *p + acc[i][j][v] : acc[i][j][v];
-            }
-        }
-}
+// Products over rows and channels (dH, dW, the encoders' and the decoder's
+// gradients) run on exact bf16 splits (gemm_split.hip).  They took 23% of a
+// step on fp32 16x16x4 products (0.54 ms of 2.5 at 64 candidates of 1,200 ops,
+// f = 128; 2.08 of 13.0 at 16 of 6,000, f = 256); 0.42 and 1.39 ms now.
+constexpr int GM = 64, GN = 64, GK = 32;   // output tile and k-step the splits over K are counted in
 
 // split count for a k-range of K rows over `tiles` output tiles: enough
 // blocks to fill the chip, at least 4 k-chunks per split
@@ -146,13 +64,14 @@ int64_t split_k_per(int64_t K, int64_t tiles, int64_t *splits) {
     return per;
 }
 
-void launch_gemm(Gemm G, bool a_kc, bool b_kc, int64_t splits, hipStream_t st) {
-    if (G.M <= 0 || G.N <= 0) return;
-    dim3 grid((unsigned)((G.M + GM - 1) / GM), (unsigned)((G.N + GN - 1) / GN), (unsigned)splits);
-    if (a_kc && b_kc) gemm_f32<true, true><<<grid, 256, 0, st>>>(G);
-    else if (a_kc) gemm_f32<true, false><<<grid, 256, 0, st>>>(G);
-    else if (b_kc) gemm_f32<false, true><<<grid, 256, 0, st>>>(G);
-    else gemm_f32<false, false><<<grid, 256, 0, st>>>(G);
+void launch_gemm(const float *A, int64_t lda, const float *B, int64_t ldb, int64_t M, int64_t N, int64_t K,
+                 int64_t ones_col, float *C, int64_t ldc, int64_t c_split, int64_t k_per, bool a_kc, int64_t splits,
+                 hipStream_t st) {
+    SplitGemm g{};
+    g.A = A; g.lda = lda; g.B = B; g.ldb = ldb;
+    g.M = M; g.N = N; g.K = K; g.ones_col = ones_col;
+    g.C = C; g.ldc = ldc; g.c_split = c_split; g.k_per = k_per;
+    launch_split_gemm(g, a_kc, false, splits, st);
 }
 
 // out[m ldo + n] (+)= sum_z P[z ps + m ldp + n], z in order
@@ -213,9 +132,8 @@ void weight_grad(const float *A, int64_t lda, const float *B, int64_t ldb, int64
     const int64_t tiles = ((M + GM - 1) / GM) * ((N + GN - 1) / GN);
     int64_t splits;
     const int64_t per = split_k_per(K, tiles, &splits);
-    Gemm g{A, lda, B, ldb, M, N, K, ones ? nb : -1, P, N, M * N, per, 0};
     prof_begin(stage, st);
-    launch_gemm(g, false, false, splits, st);
+    launch_gemm(A, lda, B, ldb, M, N, K, ones ? nb : -1, P, N, M * N, per, false, splits, st);
     prof_end(stage, st);
     launch_sum_splits(P, M * N, N, (int32_t)splits, M, nb, out, ldo, accumulate, st);
     if (ones) launch_sum_splits(P + nb, M * N, N, (int32_t)splits, M, 1, bias_out, 1, accumulate, st);
@@ -2321,12 +2239,12 @@ extern "C" tag_status tag_train_step(const tag_graph *g, const tag_model_dims *d
     dec_totals<<<1, 256, 0, stream>>>(L.loss_q, L.db2q, Q, loss, gr->dec_b2);
     dec_params<<<grid_for(H), 256, 0, stream>>>(D, gr->dec_w1, gr->dec_b1, gr->dec_w2);
     // device side: dE_dev = dT W1_dev, dW1_dev = dT^T E_dev
-    launch_gemm(Gemm{L.dT, H, w->dec_w1, din, rd, F, H, -1, L.G_dev, F, 0, H, 0}, true, false, 1, stream);
+    launch_gemm(L.dT, H, w->dec_w1, din, rd, F, H, -1, L.G_dev, F, 0, H, true, 1, stream);
     weight_grad(L.dT, H, L.E_dev, F, H, F, false, rd, L.P0, gr->dec_w1, din, nullptr, 0, stream);
     // op side: dE_op rows of the queries = dv W1_op, dW1_op = dv^T E_op[query rows]
     dec_gather_rows<<<grid_for((int64_t)Q * F), 256, 0, stream>>>(L.E_op, L.qrow, Q, F, L.Eq);
     weight_grad(L.dvq, H, L.Eq, F, H, F, false, Q, L.P1, gr->dec_w1 + F, din, nullptr, 0, stream);
-    launch_gemm(Gemm{L.dvq, H, w->dec_w1 + F, din, Q, F, H, -1, L.dEq, F, 0, H, 0}, true, false, 1, stream);
+    launch_gemm(L.dvq, H, w->dec_w1 + F, din, Q, F, H, -1, L.dEq, F, 0, H, true, 1, stream);
     fill_zero<<<grid_for(ro * F), 256, 0, stream>>>(L.G_op, ro * F);
     dec_grad_op<<<Q, 256, 0, stream>>>(L.qrow, Q, F, L.dEq, L.G_op);
     prof_end(TAG_STAGE_BWD_DECODER, stream);
@@ -2410,9 +2328,9 @@ extern "C" tag_status tag_train_step(const tag_graph *g, const tag_model_dims *d
         {
             int64_t splits;
             const int64_t per = split_k_per(rd, ((2 * F + GM - 1) / GM) * ((F + GN - 1) / GN), &splits);
-            Gemm gd{L.dY_dev, 2 * F, L.H_dev[l], F, 2 * F, F, rd, -1, L.P1, F, 2 * F * F, per, 0};
             prof_begin(TAG_STAGE_BWD_DW, stream);
-            launch_gemm(gd, false, false, splits, stream);
+            launch_gemm(L.dY_dev, 2 * F, L.H_dev[l], F, 2 * F, F, rd, -1, L.P1, F, 2 * F * F, per, false, splits,
+                        stream);
             prof_end(TAG_STAGE_BWD_DW, stream);
             float *g1 = gW + (size_t)F * 2 * F;
             launch_sum_splits(L.P1, 2 * F * F, F, (int32_t)splits, F, F, g1, 2 * F, 1, stream);
@@ -2421,11 +2339,10 @@ extern "C" tag_status tag_train_step(const tag_graph *g, const tag_model_dims *d
         }
         // dH = dY [W^h ; W^h'] (overwrites the layer-output gradients, no longer needed)
         prof_begin(TAG_STAGE_BWD_DH, stream);
-        launch_gemm(Gemm{L.dY_op, 2 * F, Wl, 2 * F, ro, F, 2 * F, -1, L.G_op, F, 0, 2 * F, 0}, true, false, 1, stream);
+        launch_gemm(L.dY_op, 2 * F, Wl, 2 * F, ro, F, 2 * F, -1, L.G_op, F, 0, 2 * F, true, 1, stream);
         prof_end(TAG_STAGE_BWD_DH, stream);
         prof_begin(TAG_STAGE_BWD_DH, stream);
-        launch_gemm(Gemm{L.dY_dev, 2 * F, Wl + (size_t)F * 2 * F, 2 * F, rd, F, 2 * F, -1, L.G_dev, F, 0, 2 * F, 0},
-                    true, false, 1, stream);
+        launch_gemm(L.dY_dev, 2 * F, Wl + (size_t)F * 2 * F, 2 * F, rd, F, 2 * F, -1, L.G_dev, F, 0, 2 * F, true, 1, stream);
         prof_end(TAG_STAGE_BWD_DH, stream);
     }
 
