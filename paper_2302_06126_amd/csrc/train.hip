@@ -836,16 +836,17 @@ __global__ void bwd_combine(BwdLayer P, BwdSrc S, int K) {
 struct OdTile {
     const int32_t *tiles;          // [n_tiles][3]: first op (global), op count, topology
     const int32_t *dev_off;        // [G+1]
-    const int32_t *rp, *col, *eid; // op<-device bucket (rows: ops)
+    const int32_t *rp;             // op<-device bucket (rows: ops)
+    const uint64_t *omask;         // [R*n_op][2]: link and placement-bit masks over the local devices
     int64_t n_op, n_dev, n_slots;
     const float *Y_op, *Y_dev;     // saved Y rows, od half at +F
     const float *dO_op, *dO_dev;   // gradient rows of the layer outputs
     float gamma;
-    float *SA1, *SD1, *SA2, *SD2;  // slots of op<-device and device<-op entries
+    float *S2, *D2;                // [R][K][n_slots] device<-op logits and their gradients
     float *Zop, *Zdev;             // [rows][2][K]; od at 1 (written by the tile kernels)
     float *dY_op, *dY_dev;         // od halves: dY_op + F, dY_dev + 0
     float *PD;                     // [R][n_tiles][max_dev][F] device partials
-    int32_t max_dev, n_tiles;
+    int32_t K, max_dev, n_tiles;
     const int32_t *tile_off;       // [G+1]
     float *part;                   // [4][nb][F] parameter partials (da, dU0, dU1, dc')
     // softmax of both op-device directions inside the tile kernels
@@ -856,88 +857,6 @@ struct OdTile {
     float *part_a2;                // [ceil(R*n_dev/4)][F] d adst sums over device rows
 };
 
-// LDS row stride of the staged device rows (+4 floats: the four entry
-// groups of a wavefront read different rows at the same channels)
-template <int F>
-constexpr int od_stride() { return F + 4; }
-
-// Block set-up of the tile kernels: the tile's row pointers, one byte per
-// tile entry (local device index | placement bit << 7, read coalesced from
-// the entry range of the tile), and the device rows of the tile's topology:
-// messages for both bits, gamma dO rows and (TERMS) attention logit terms
-// and destination terms.
-template <int F, int K, bool ELU, bool TERMS>
-__device__ void od_stage(const BwdLayer &P, const OdTile &T, int32_t rep, int32_t u0, int32_t n, int32_t d0,
-                         int32_t nd, float *md, float *dod, float *pd, float *qdd, int32_t *rps, uint8_t *ent) {
-    constexpr int D = F / K, FS = od_stride<F>();
-    constexpr int RU = 8, EU = 4;   // loads issued together per thread (rows, entries)
-    const float *a = P.att_src + F, *ad = P.att_dst + F, *cp = P.cp + F;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    for (int i = tid; i <= n; i += nt) rps[i] = T.rp[u0 + i];
-    const int32_t e0 = T.rp[u0], ne = T.rp[u0 + n] - e0;
-    const uint8_t *xb = P.x_od + (int64_t)rep * P.s_od;
-    for (int i0 = tid; i0 < ne; i0 += EU * nt) {
-        int32_t cl[EU], id[EU];
-#pragma unroll
-        for (int j = 0; j < EU; ++j) {
-            const int i = min(i0 + j * nt, ne - 1);
-            cl[j] = T.col[e0 + i];
-            id[j] = T.eid[e0 + i];
-        }
-        uint8_t xv[EU];
-#pragma unroll
-        for (int j = 0; j < EU; ++j) xv[j] = xb[id[j]];
-#pragma unroll
-        for (int j = 0; j < EU; ++j)
-            if (i0 + j * nt < ne) ent[i0 + j * nt] = (uint8_t)((cl[j] - d0) | (xv[j] ? 0x80 : 0));
-    }
-    const int total = nd * F;
-    for (int i0 = tid; i0 < total; i0 += RU * nt) {
-        float y[RU], g[RU], u[RU];
-#pragma unroll
-        for (int j = 0; j < RU; ++j) {
-            const int i = min(i0 + j * nt, total - 1);
-            const int v = i / F, c = i % F;
-            const int64_t row = (int64_t)rep * T.n_dev + d0 + v;
-            y[j] = T.Y_dev[row * 2 * F + F + c];
-            g[j] = T.dO_dev[row * F + c];
-            u[j] = P.U[((int64_t)F + c) * 2 + 0];
-        }
-#pragma unroll
-        for (int j = 0; j < RU; ++j) {
-            const int i = i0 + j * nt;
-            if (i < total) {
-                const int v = i / F, c = i % F;
-                md[(v * 2 + 0) * FS + c] = msg_act<ELU>(y[j]);
-                md[(v * 2 + 1) * FS + c] = msg_act<ELU>(y[j] + u[j]);
-                dod[v * FS + c] = T.gamma * g[j];
-            }
-        }
-    }
-    if constexpr (TERMS) {
-        __syncthreads();
-        for (int i = tid; i < nd * 3 * K; i += nt) {
-            const int v = i / (3 * K), r = i % (3 * K), x = r / K, k = r % K;
-            float t = 0.f;
-            if (x < 2) {
-                for (int c = k * D; c < (k + 1) * D; ++c) t = fmaf(a[c], md[(v * 2 + x) * FS + c], t);
-                pd[(v * 2 + x) * K + k] = t;
-            } else {
-                const float *y = T.Y_dev + ((int64_t)rep * T.n_dev + d0 + v) * 2 * F + F;
-                for (int c = k * D; c < (k + 1) * D; ++c) t = fmaf(ad[c], y[c] - cp[c], t);
-                qdd[v * K + k] = t;
-            }
-        }
-    }
-    __syncthreads();
-}
-
-// Lane layout of the tile kernels: a wavefront takes four entries of an op
-// at a time, 16 lanes per entry, f/16 consecutive channels per lane; a
-// head spans 16/K lanes (K <= 16).  Each wavefront walks ops u0 + wv,
-// u0 + wv + 4, ... and reads the rows of its next op while it works on the
-// current one.  Slots of op-device entries are keyed by their position in
-// the op<-device bucket.
 // max over aligned groups of 16 lanes (DPP inside a 16-lane row)
 __device__ __forceinline__ float row_max16(float v) {
     auto dpp = [](float x, auto ctrl) {
@@ -950,195 +869,305 @@ __device__ __forceinline__ float row_max16(float v) {
     return v;
 }
 
-// Scores on the matrix cores (topologies of at most 16 devices): wavefront w
-// takes the tile's ops 16 w .. 16 w + 15; per head and placement bit b the
-// logit gradients dO_u . m_b(v) (op <- device) and dO_v . m_b(u) (device <-
-// op) are fp32 MFMA 16x16x4 products over the head's channels, lane l
-// supplying op 16 w + l % 16 (A) and device l % 16 (B) at channel slice
-// l / 16.  Result register r of lane l is op 16 w + 4 (l / 16) + r, device
-// l % 16: an op row's entries lie in the 16 lanes of one lane group, so its
-// softmax (op <- device) reduces over those lanes; the device<-op records
-// fold per lane over its four ops, then over lane groups and wavefronts in order.
-template <int F, int K, bool ELU>
+// sum over the four lane groups of a wavefront (lanes l, l + 16, l + 32, l + 48)
+__device__ __forceinline__ float group_sum4(float v) {
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
+}
+
+// derivative of sigma from its output: ReLU [m > 0]; ELU 1 or e^z = m + 1
+template <bool ELU>
+__device__ __forceinline__ float dact(float m) { return m > 0.f ? 1.f : (ELU ? m + 1.f : 0.f); }
+
+// Op-device tile kernels: one block per (candidate, tile of 64 ops), all
+// device rows of the tile's topology in DB blocks of 16, one head at a time
+// (D = F/K channels, a multiple of 16).  An op-device link carries one bit, so
+// every product over a tile's links is a dense contraction on fp32 16x16x4
+// MFMAs over (op, device) with each link's scalar in the half of its bit.
+// Operands come from memory: lane l of a wavefront reads row l % 16 (op or
+// device) and channels 16 t + 4 (l / 16) .. + 3 as one 16-byte load that feeds
+// four steps, or (contractions over ops or devices) whole 64-byte row
+// segments; the rows repeat between wavefronts and blocks of a candidate, so
+// they come from L1 and L2 (blocks of a candidate share an XCD), and LDS holds
+// only one head's scalars, so 64 devices fit and several blocks share a CU.
+// The work per link and channel is on the matrix cores; what is left per link
+// and head are the softmax scalars.  This replaces kernels that held all
+// device rows in LDS (at most 16 devices) and formed the op side per link on
+// the vector pipe (64 candidates of 1,200 ops and 16 devices, f = 128: scores
+// 143 -> 78 us, messages 135 -> 51 us a layer), and, for more devices or f =
+// 256, passes that walked every link of both directions twice (16 candidates
+// of 6,000 ops and 32 devices: 2.6 -> 0.36 ms a layer).
+constexpr int kAwS = kOpTile + 4;   // row stride of aw: its operand reads fall on distinct banks
+
+// (candidate, tile) of this block, the tiles of a candidate on one XCD
+__device__ __forceinline__ void od_block(const OdTile &T, int32_t &t, int32_t &rep) {
+    const uint32_t lb = xcd_swizzle(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+    t = (int32_t)(lb % gridDim.x);
+    rep = (int32_t)(lb / gridDim.x);
+}
+
+// Logits and their gradients of both directions, the op<-device softmax and
+// its device side.  Wavefront w takes ops 16 w .. 16 w + 15 as A rows and the
+// devices as B columns; result register r of lane l is op 16 w + 4 (l / 16) +
+// r, device 16 db + l % 16, so an op row's softmax reduces in-lane over the
+// device blocks and then over a lane group.  alpha goes to aw[device][op]
+// (placement bit in the sign bit) and dz into per-bit sums; then sum_u alpha
+// gamma dO_u per bit is a (devices x 64 ops) by (64 ops x channels) product,
+// with sigma' of the device's message and the a Z terms applied once per
+// (device, channel).  device<-op records (max, sum, weighted sum) fold per
+// lane over its ops, then over lane groups and wavefronts in order.
+template <bool ELU, int DB>
 __global__ void __launch_bounds__(256) bwd_od_scores(BwdLayer P, OdTile T) {
-    constexpr int D = F / K, FS = od_stride<F>(), CPL = F / 64;
-    constexpr int HG = K >= 2 ? 2 : 1;   // heads per pass over the channels (register budget)
-    static_assert(K <= 16 && D >= 16, "the op-device tile path needs heads of at least 16 channels");
-    extern __shared__ float sh[];
-    __shared__ int32_t rps[kOpTile + 1];
+    constexpr int MDP = 16 * DB;
+    __shared__ __attribute__((aligned(16))) float cst[4][256];         // U (bit column), a, a~, c' of the relation
+    __shared__ __attribute__((aligned(16))) float aw[MDP * kAwS];
+    __shared__ float z1[4][2][MDP];                                    // dz sums per wavefront and bit
+    __shared__ float drc[4][MDP][3];
+    __shared__ float dpart[3][DB][256];                                // device side of d a, dU0, dc'
+    __shared__ int32_t rps[kOpTile];
     __shared__ uint64_t pres[kOpTile], bits[kOpTile];
-    __shared__ float zop[kOpTile][K];   // Z of the tile's op rows (op <- device)
-    __shared__ float red[4][F];
-    __shared__ float cst[4][F];         // U (bit column), a, a~, c' of the relation
-    const int32_t t = blockIdx.x, rep = blockIdx.y;
+    int32_t t, rep;
+    od_block(T, t, rep);
+    const int F = P.F, K = T.K, D = F / K;
     const int32_t u0 = T.tiles[3 * t], n = T.tiles[3 * t + 1], g = T.tiles[3 * t + 2];
     const int32_t d0 = T.dev_off[g], nd = T.dev_off[g + 1] - d0;
-    const int MD = T.max_dev;
-    float *md = sh, *dod = md + 2 * MD * FS, *pd = dod + MD * FS, *qdd = pd + 2 * MD * K;
-    float *dst = qdd + MD * K;           // [4][16][K][3] device<-op records per wavefront
-    uint8_t *ent = reinterpret_cast<uint8_t *>(dst + 4 * 16 * K * 3);
-    for (int i = threadIdx.x; i < 4 * 16 * K; i += blockDim.x) {
-        dst[3 * i] = -INFINITY;
-        dst[3 * i + 1] = dst[3 * i + 2] = 0.f;
-    }
-    for (int i = threadIdx.x; i < F; i += blockDim.x) {
+    const int64_t tb = (int64_t)rep * T.n_tiles + t, op0 = (int64_t)rep * T.n_op + u0, dv0 = (int64_t)rep * T.n_dev + d0;
+    for (int i = threadIdx.x; i < F; i += 256) {
         cst[0][i] = P.U[((int64_t)F + i) * 2 + 0];
         cst[1][i] = P.att_src[F + i];
         cst[2][i] = P.att_dst[F + i];
         cst[3][i] = P.cp[F + i];
     }
-    od_stage<F, K, ELU, true>(P, T, rep, u0, n, d0, nd, md, dod, pd, qdd, rps, ent);
-    // link and placement-bit masks of the tile's ops over the topology's devices
     if (threadIdx.x < kOpTile) {
-        uint64_t pr = 0ull, bt = 0ull;
-        if ((int)threadIdx.x < n)
-            for (int32_t e = rps[threadIdx.x]; e < rps[threadIdx.x + 1]; ++e) {
-                const int eb = ent[e - rps[0]];
-                pr |= 1ull << (eb & 0x7f);
-                if (eb >> 7) bt |= 1ull << (eb & 0x7f);
-            }
-        pres[threadIdx.x] = pr;
-        bits[threadIdx.x] = bt;
+        const int i = threadIdx.x;
+        const bool in = i < n;
+        rps[i] = in ? T.rp[u0 + i] : 0;
+        pres[i] = in ? T.omask[2 * (op0 + i)] : 0ull;
+        bits[i] = in ? T.omask[2 * (op0 + i) + 1] : 0ull;
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lr = lane & 15, lg = lane >> 4;
-    const int ua = 16 * wv + lr;                       // op this lane supplies (A rows)
-    const bool aok = ua < n;
-    const int64_t rowa = (int64_t)rep * T.n_op + u0 + (aok ? ua : 0);
+    // the lane's op row and device rows as operands (rows past the end repeat
+    // a row of the tile: their links are absent)
+    const int64_t rowa = op0 + min(16 * wv + lr, n - 1);
     const float *ya = T.Y_op + rowa * 2 * F + F, *da = T.dO_op + rowa * F;
-    const bool vok = lr < nd;                          // device of this lane's column (B, results)
-    const int64_t sbase = (int64_t)rep * T.n_slots;
-    for (int hg = 0; hg < K; hg += HG) {
-        f4 d1[HG][2], d2[HG][2];
-        float qv[HG], p0v[HG], p1v[HG];                // this lane's parts of the op's head terms
+    const float *yv[DB], *gv[DB];
 #pragma unroll
-        for (int j = 0; j < HG; ++j) {
-            d1[j][0] = d1[j][1] = d2[j][0] = d2[j][1] = f4{0.f, 0.f, 0.f, 0.f};
-            qv[j] = p0v[j] = p1v[j] = 0.f;
+    for (int db = 0; db < DB; ++db) {
+        const int64_t row = dv0 + min(16 * db + lr, nd - 1);
+        yv[db] = T.Y_dev + row * 2 * F + F;
+        gv[db] = T.dO_dev + row * F;
+    }
+    struct Frag { float4 y, g, yd[DB], gd[DB]; };
+    auto load = [&](int c, Frag &f) {
+        f.y = *reinterpret_cast<const float4 *>(ya + c);
+        f.g = *reinterpret_cast<const float4 *>(da + c);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            f.yd[db] = *reinterpret_cast<const float4 *>(yv[db] + c);
+            f.gd[db] = *reinterpret_cast<const float4 *>(gv[db] + c);
         }
-        // one pass over the channels of heads hg .. hg + HG - 1
+    };
+    auto at = [](const float4 &v, int s) { return s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w; };
+    Frag cur;
+    load(4 * lg, cur);
+    for (int h = 0; h < K; ++h) {
+        f4 d1[2][DB], d2[2][DB];
+        float qp = 0.f, p0p = 0.f, p1p = 0.f, qd[DB], pd0[DB], pd1[DB];   // the lane's parts of its rows' head terms
 #pragma unroll
-        for (int kk = 0; kk < HG * D / 4; ++kk) {
-            const int j = kk / (D / 4);
-            const int c = hg * D + 4 * kk + lg;
-            const float y = aok ? ya[c] : 0.f;
-            const float gd = aok ? T.gamma * da[c] : 0.f;
-            const float m0 = aok ? msg_act<ELU>(y) : 0.f;
-            const float m1 = aok ? msg_act<ELU>(y + cst[0][c]) : 0.f;
-            const float as = cst[1][c];
-            qv[j] = fmaf(cst[2][c], y - cst[3][c], qv[j]);
-            p0v[j] = fmaf(as, m0, p0v[j]);
-            p1v[j] = fmaf(as, m1, p1v[j]);
-            const float bm0 = vok ? md[(lr * 2 + 0) * FS + c] : 0.f, bm1 = vok ? md[(lr * 2 + 1) * FS + c] : 0.f;
-            const float bd = vok ? dod[lr * FS + c] : 0.f;
-            d1[j][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(gd, bm0, d1[j][0], 0, 0, 0);
-            d1[j][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(gd, bm1, d1[j][1], 0, 0, 0);
-            d2[j][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(m0, bd, d2[j][0], 0, 0, 0);
-            d2[j][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(m1, bd, d2[j][1], 0, 0, 0);
+        for (int db = 0; db < DB; ++db) {
+            d1[0][db] = d1[1][db] = d2[0][db] = d2[1][db] = f4{0.f, 0.f, 0.f, 0.f};
+            qd[db] = pd0[db] = pd1[db] = 0.f;
         }
+        for (int c = h * D + 4 * lg; c < (h + 1) * D; c += 16) {
+            Frag nxt;
+            load(c + 16 < F ? c + 16 : 4 * lg, nxt);   // (also the next head's first channels)
+            const float4 u4 = *reinterpret_cast<const float4 *>(&cst[0][c]), a4 = *reinterpret_cast<const float4 *>(&cst[1][c]);
+            const float4 b4 = *reinterpret_cast<const float4 *>(&cst[2][c]), c4 = *reinterpret_cast<const float4 *>(&cst[3][c]);
 #pragma unroll
-        for (int j = 0; j < HG; ++j) {
-        const int h = hg + j;
-        // the op's head terms: sums over the four channel slices (lane groups)
-        float qp = qv[j], p0p = p0v[j], p1p = p1v[j];
-        qp += __shfl_xor(qp, 16, 64); qp += __shfl_xor(qp, 32, 64);
-        p0p += __shfl_xor(p0p, 16, 64); p0p += __shfl_xor(p0p, 32, 64);
-        p1p += __shfl_xor(p1p, 16, 64); p1p += __shfl_xor(p1p, 32, 64);
-        float dmx = -INFINITY, dden = 0.f, dnum = 0.f;   // device<-op record of this lane's device
+            for (int s = 0; s < 4; ++s) {
+                const float U = at(u4, s), as = at(a4, s), ad = at(b4, s), cp = at(c4, s);
+                const float y = at(cur.y, s), gd = T.gamma * at(cur.g, s);
+                const float m0 = msg_act<ELU>(y), m1 = msg_act<ELU>(y + U);
+                qp = fmaf(ad, y - cp, qp);
+                p0p = fmaf(as, m0, p0p);
+                p1p = fmaf(as, m1, p1p);
+#pragma unroll
+                for (int db = 0; db < DB; ++db) {
+                    const float yy = at(cur.yd[db], s), bd = T.gamma * at(cur.gd[db], s);
+                    const float b0 = msg_act<ELU>(yy), b1 = msg_act<ELU>(yy + U);
+                    qd[db] = fmaf(ad, yy - cp, qd[db]);
+                    pd0[db] = fmaf(as, b0, pd0[db]);
+                    pd1[db] = fmaf(as, b1, pd1[db]);
+                    d1[0][db] = __builtin_amdgcn_mfma_f32_16x16x4f32(gd, b0, d1[0][db], 0, 0, 0);
+                    d1[1][db] = __builtin_amdgcn_mfma_f32_16x16x4f32(gd, b1, d1[1][db], 0, 0, 0);
+                    d2[0][db] = __builtin_amdgcn_mfma_f32_16x16x4f32(m0, bd, d2[0][db], 0, 0, 0);
+                    d2[1][db] = __builtin_amdgcn_mfma_f32_16x16x4f32(m1, bd, d2[1][db], 0, 0, 0);
+                }
+            }
+            cur = nxt;
+        }
+        qp = group_sum4(qp); p0p = group_sum4(p0p); p1p = group_sum4(p1p);
+        float dmx[DB], dden[DB], dnum[DB], zb[2][DB], av[DB][4];
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            qd[db] = group_sum4(qd[db]); pd0[db] = group_sum4(pd0[db]); pd1[db] = group_sum4(pd1[db]);
+            dmx[db] = -INFINITY;
+            dden[db] = dnum[db] = zb[0][db] = zb[1][db] = 0.f;
+        }
+        float *S2 = T.S2 + ((int64_t)rep * K + h) * T.n_slots, *D2 = T.D2 + ((int64_t)rep * K + h) * T.n_slots;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int u = 16 * wv + 4 * lg + r;          // the op of result register r
-            const int src = 4 * lg + r;                  // a lane supplying op u
+            const int src = 4 * lg + r, u = 16 * wv + src;   // the register's op; a lane supplying it
             const float qu = __shfl(qp, src, 64), p0u = __shfl(p0p, src, 64), p1u = __shfl(p1p, src, 64);
-            const uint64_t pr = u < n ? pres[u] : 0ull, bt = u < n ? bits[u] : 0ull;
-            const bool ok = vok && ((pr >> lr) & 1ull);
-            const int x = (int)((bt >> lr) & 1ull);
-            const float dd1 = x ? d1[j][1][r] : d1[j][0][r], dd2 = x ? d2[j][1][r] : d2[j][0][r];
-            const float s1 = ok ? leaky(pd[(lr * 2 + x) * K + h] + qu, P.slope) : -INFINITY;   // op <- device
-            const float s2 = leaky((x ? p1u : p0u) + (vok ? qdd[lr * K + h] : 0.f), P.slope);   // device <- op
-            const int32_t e = ok ? rps[u] + __popcll(pr & ((1ull << lr) - 1ull)) : 0;
-            if (ok) {
-                const int64_t idx = (sbase + e) * K + h;
-                T.SA2[idx] = s2;
-                T.SD2[idx] = dd2;
-                softmax_fold(s2, dd2, dmx, dden, dnum);
+            const uint64_t pr = pres[u], bt = bits[u];
+            bool ok[DB], x[DB];
+            float s1[DB], dd1[DB], mx = -INFINITY;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const int v = 16 * db + lr;
+                ok[db] = (pr >> v) & 1ull;
+                x[db] = (bt >> v) & 1ull;
+                dd1[db] = x[db] ? d1[1][db][r] : d1[0][db][r];
+                s1[db] = ok[db] ? leaky((x[db] ? pd1[db] : pd0[db]) + qu, P.slope) : -INFINITY;   // op <- device
+                mx = fmaxf(mx, s1[db]);
+                if (ok[db]) {   // device <- op
+                    const float s2 = leaky((x[db] ? p1u : p0u) + qd[db], P.slope);
+                    const float dd2 = x[db] ? d2[1][db][r] : d2[0][db][r];
+                    const int32_t e = rps[u] + __popcll(pr & ((1ull << v) - 1ull));
+                    S2[e] = s2;
+                    D2[e] = dd2;
+                    softmax_fold(s2, dd2, dmx[db], dden[db], dnum[db]);
+                }
             }
-            // softmax of op u's row over its devices (the lane group)
-            const float mx = row_max16(s1);
-            const float ex = ok ? __expf(s1 - mx) : 0.f;
-            const float den = row_sum<16>(ex), num = row_sum<16>(ex * dd1);
+            // softmax of op u's row over its devices
+            mx = row_max16(mx);
+            float ex[DB], den = 0.f, num = 0.f, zs = 0.f;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                ex[db] = ok[db] ? __expf(s1[db] - mx) : 0.f;
+                den += ex[db];
+                num = fmaf(ex[db], dd1[db], num);
+            }
+            den = row_sum<16>(den);
+            num = row_sum<16>(num);
             const float inv = den > 0.f ? 1.f / den : 0.f, cc = num * inv;
-            const float al = ex * inv;
-            const float dz = ok ? al * (dd1 - cc) * (s1 > 0.f ? 1.f : P.slope) : 0.f;
-            if (ok) {
-                const int64_t idx = (sbase + e) * K + h;
-                T.SA1[idx] = al;
-                T.SD1[idx] = dz;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const float al = ex[db] * inv;
+                const float dz = ok[db] ? al * (dd1[db] - cc) * (s1[db] > 0.f ? 1.f : P.slope) : 0.f;
+                av[db][r] = __int_as_float(__float_as_int(al) | (x[db] ? INT_MIN : 0));
+                zb[0][db] += x[db] ? 0.f : dz;
+                zb[1][db] += x[db] ? dz : 0.f;
+                zs += dz;
             }
-            const float zs = row_sum<16>(dz);
-            if (lr == 0 && u < n) {
-                zop[u][h] = zs;
-                T.Zop[(((int64_t)rep * T.n_op + u0 + u) * 2 + 1) * K + h] = zs;
+            zs = row_sum<16>(zs);
+            if (lr == 0 && u < n) T.Zop[((op0 + u) * 2 + 1) * K + h] = zs;
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const int v = 16 * db + lr;
+            *reinterpret_cast<float4 *>(&aw[v * kAwS + 16 * wv + 4 * lg]) =
+                make_float4(av[db][0], av[db][1], av[db][2], av[db][3]);
+            const float z0 = group_sum4(zb[0][db]), zz = group_sum4(zb[1][db]);
+            // this wavefront's record of device v: its lane groups in order
+            for (int o = 16; o < 64; o <<= 1) {
+                const float m2 = __shfl_xor(dmx[db], o, 64), dv = __shfl_xor(dden[db], o, 64), nv = __shfl_xor(dnum[db], o, 64);
+                softmax_merge(m2, dv, nv, dmx[db], dden[db], dnum[db]);
+            }
+            if (lg == 0) {
+                z1[wv][0][v] = z0;
+                z1[wv][1][v] = zz;
+                drc[wv][v][0] = dmx[db]; drc[wv][v][1] = dden[db]; drc[wv][v][2] = dnum[db];
             }
         }
-        // this wavefront's record of device lr: its lane groups in order
-        for (int o = 16; o < 64; o <<= 1) {
-            const float m2 = __shfl_xor(dmx, o, 64), d2v = __shfl_xor(dden, o, 64), n2 = __shfl_xor(dnum, o, 64);
-            softmax_merge(m2, d2v, n2, dmx, dden, dnum);
+        __syncthreads();
+        // the tile's device<-op records of head h, wavefronts in order
+        if ((int)threadIdx.x < nd) {
+            const int v = threadIdx.x;
+            float mx = drc[0][v][0], den = drc[0][v][1], num = drc[0][v][2];
+            for (int w = 1; w < 4; ++w) softmax_merge(drc[w][v][0], drc[w][v][1], drc[w][v][2], mx, den, num);
+            float *r = T.drec + ((tb * T.max_dev + v) * K + h) * 3;
+            r[0] = mx; r[1] = den; r[2] = num;
         }
-        if (lg == 0) {
-            float *st = dst + ((wv * 16 + lr) * K + h) * 3;
-            st[0] = dmx; st[1] = dden; st[2] = dnum;
+        // device side of op<-device: (device block, 16-channel block) pairs over the wavefronts
+        for (int p = wv; p < DB * (D / 16); p += 4) {
+            const int db = p % DB, cl = h * D + (p / DB) * 16 + lr;
+            float bo[kOpTile / 4], ym[4];
+#pragma unroll
+            for (int ks = 0; ks < kOpTile / 4; ++ks)
+                bo[ks] = T.gamma * T.dO_op[(op0 + min(4 * ks + lg, n - 1)) * F + cl];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ym[r] = T.Y_dev[(dv0 + min(16 * db + 4 * lg + r, nd - 1)) * 2 * F + F + cl];
+            f4 t0 = f4{0.f, 0.f, 0.f, 0.f}, t1 = f4{0.f, 0.f, 0.f, 0.f};
+            const float *arow = aw + (16 * db + lr) * kAwS + lg;
+#pragma unroll
+            for (int ks = 0; ks < kOpTile / 4; ++ks) {
+                const float w = arow[4 * ks];
+                const bool bit = __float_as_int(w) < 0;
+                t0 = __builtin_amdgcn_mfma_f32_16x16x4f32(bit ? 0.f : w, bo[ks], t0, 0, 0, 0);
+                t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(bit ? -w : 0.f, bo[ks], t1, 0, 0, 0);
+            }
+            const float ac = cst[1][cl], U = cst[0][cl];
+            float sga = 0.f, sgu = 0.f, sgc = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int v = 16 * db + 4 * lg + r;
+                if (v < nd) {
+                    // the wavefronts' dz sums in order
+                    const float zb0 = (z1[0][0][v] + z1[1][0][v]) + (z1[2][0][v] + z1[3][0][v]);
+                    const float zb1 = (z1[0][1][v] + z1[1][1][v]) + (z1[2][1][v] + z1[3][1][v]);
+                    const float mb0 = msg_act<ELU>(ym[r]), mb1 = msg_act<ELU>(ym[r] + U);
+                    const float p0 = dact<ELU>(mb0) * fmaf(ac, zb0, t0[r]);
+                    const float p1 = dact<ELU>(mb1) * fmaf(ac, zb1, t1[r]);
+                    T.PD[(tb * T.max_dev + v) * F + cl] = p0 + p1;
+                    sga = fmaf(mb0, zb0, fmaf(mb1, zb1, sga));
+                    sgu += p1;
+                    sgc += p0 + p1;
+                }
+            }
+            sga = group_sum4(sga); sgu = group_sum4(sgu); sgc = group_sum4(sgc);
+            if (lane < 16) { dpart[0][db][cl] = sga; dpart[1][db][cl] = sgu; dpart[2][db][cl] = sgc; }
         }
-        }
+        __syncthreads();   // aw, z1 and the records are free for the next head
     }
-    // d adst of the op rows: sum over the wavefront's ops of Z_u (Y_u - c'), lanes over channels
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    {
-        float acc[CPL];
-        for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-        const int cc0 = lane * CPL, hh = cc0 / D;
-        for (int uu = 0; uu < 16; ++uu) {
-            const int u = 16 * wv + uu;
-            if (u >= n) break;
-            float y[CPL];
-            load_ch<CPL, false>(T.Y_op, ((int64_t)rep * T.n_op + u0 + u) * 2 * F + F + cc0, y);
-            const float z = zop[u][hh];
-            for (int c = 0; c < CPL; ++c) acc[c] = fmaf(z, y[c] - cst[3][cc0 + c], acc[c]);
+    // the block's device-side parameter sums (the messages kernel adds the op side)
+    const int64_t nb = (int64_t)gridDim.x * gridDim.y;
+    for (int c = threadIdx.x; c < F; c += 256) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            float s = dpart[q][0][c];
+#pragma unroll
+            for (int db = 1; db < DB; ++db) s += dpart[q][db][c];
+            T.part[((int64_t)(q == 2 ? 3 : q) * nb + tb) * F + c] = s;
         }
-        for (int c = 0; c < CPL; ++c) red[wv][cc0 + c] = acc[c];
-    }
-    __syncthreads();
-    // the tile's sums of d adst (op rows) and device<-op records, wavefronts in order
-    const int64_t tb = (int64_t)rep * T.n_tiles + t;
-    for (int c = threadIdx.x; c < F; c += 256) T.part_a1[tb * F + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
-    for (int i = threadIdx.x; i < nd * K; i += blockDim.x) {
-        float mx = dst[3 * i], den = dst[3 * i + 1], num = dst[3 * i + 2];
-        for (int w = 1; w < 4; ++w) {
-            const float *o = dst + ((size_t)w * 16 * K + i) * 3;
-            softmax_merge(o[0], o[1], o[2], mx, den, num);
-        }
-        float *r = T.drec + ((tb * MD) * K + i) * 3;
-        r[0] = mx; r[1] = den; r[2] = num;
+        T.part[(2 * nb + tb) * F + c] = 0.f;   // no dU1 for od
     }
 }
 
 // device<-op softmax statistics: per (candidate, device, head) the tiles'
-// records of the device's topology merged in tile order
-__global__ void bwd_od_dev_stats(BwdLayer P, OdTile T, const int32_t *dev_topo, int K) {
-    const int64_t total = (int64_t)P.R * T.n_dev * K;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t row = i / K;
-        const int h = (int)(i % K);
-        const int32_t rep = (int32_t)(row / T.n_dev), d = (int32_t)(row % T.n_dev);
-        const int32_t g = dev_topo[d], v = d - T.dev_off[g];
-        float mx = -INFINITY, den = 0.f, num = 0.f;
-        for (int32_t t = T.tile_off[g]; t < T.tile_off[g + 1]; ++t) {
-            const float *r = T.drec + ((((int64_t)rep * T.n_tiles + t) * T.max_dev + v) * K + h) * 3;
-            softmax_merge(r[0], r[1], r[2], mx, den, num);
-        }
+// records of the device's topology, one wavefront each: a lane merges every
+// 64th tile's record in order, then the lanes in a fixed tree (one thread per
+// statistic was a serial chain over the tiles: 54 us for 94 tiles,
+// 6 us now)
+__global__ void __launch_bounds__(256) bwd_od_dev_stats(BwdLayer P, OdTile T, const int32_t *dev_topo, int K) {
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= (int64_t)P.R * T.n_dev * K) return;
+    const int lane = threadIdx.x & 63;
+    const int64_t row = i / K;
+    const int h = (int)(i % K);
+    const int32_t rep = (int32_t)(row / T.n_dev), d = (int32_t)(row % T.n_dev);
+    const int32_t g = dev_topo[d], v = d - T.dev_off[g];
+    float mx = -INFINITY, den = 0.f, num = 0.f;
+    for (int32_t t = T.tile_off[g] + lane; t < T.tile_off[g + 1]; t += 64) {
+        const float *r = T.drec + ((((int64_t)rep * T.n_tiles + t) * T.max_dev + v) * K + h) * 3;
+        softmax_merge(r[0], r[1], r[2], mx, den, num);
+    }
+    for (int o = 1; o < 64; o <<= 1) {
+        const float m2 = __shfl_xor(mx, o, 64), d2 = __shfl_xor(den, o, 64), n2 = __shfl_xor(num, o, 64);
+        softmax_merge(m2, d2, n2, mx, den, num);
+    }
+    if (lane == 0) {
         const float inv = den > 0.f ? 1.f / den : 0.f;
         T.dstat[i * 3 + 0] = mx;
         T.dstat[i * 3 + 1] = inv;
@@ -1146,266 +1175,199 @@ __global__ void bwd_od_dev_stats(BwdLayer P, OdTile T, const int32_t *dev_topo, 
     }
 }
 
-// derivative of sigma from its output: ReLU [m > 0]; ELU 1 or e^z = m + 1
-template <bool ELU>
-__device__ __forceinline__ float dact(float m) { return m > 0.f ? 1.f : (ELU ? m + 1.f : 0.f); }
-
-// The (alpha, dz) scalars of an op's entries come in chunks of 64 / K
-// entries, lane i holding entry i / K, head i % K of the chunk (one
-// coalesced read per array); the first chunk of the next op is read ahead.
-// Op side per entry (the wavefront's op is the source of device<-op links):
-// dY of the op row and the op's parts of d a, dU0 and dc'.  Device side
-// (op<-device links, the devices are the sources): each entry's alpha goes
-// into a dense per-head matrix aw[h][device][op] (the placement bit in the
-// sign bit; alpha >= 0) and its dz into per-bit sums; after the tile's ops,
-// sum_u alpha_uv gamma dO_u[c] for each placement bit is a (devices x 64 ops)
-// by (64 ops x channels) product on the matrix cores, and sigma' of the
-// device's message, the a Z terms and the device parts of d a, dU0 and dc'
-// are applied once per (device, channel).
-constexpr int kAS = 68;   // row stride of aw: the 16 x 4 operand reads fall on distinct banks
-
-template <int F, int K, bool ELU>
+// Op side of device<-op: per link and head (alpha, dz) from the stored logits
+// and the device's merged statistics, 16 lanes per op over its devices.  The
+// op's part of dY is then sum_v alpha gamma dO_v for each placement bit, a (16
+// ops x devices) by (devices x channels) product per wavefront, with sigma' of
+// the op's two messages and the a z terms applied once per (op, channel); the
+// op rows' parts of d a, dU0, dc' and d adst ride along.
+template <bool ELU, int DB>
 __global__ void __launch_bounds__(256) bwd_od_messages(BwdLayer P, OdTile T) {
-    constexpr int CPE = F / 16, FS = od_stride<F>(), EPC = 64 / K, D = F / K;
-    constexpr bool AHEAD = CPE <= 8;   // read the next op's rows ahead (register budget)
-    static_assert(K <= 16 && D >= 16, "the op-device tile path needs heads of at least 16 channels");
-    extern __shared__ float sh[];
-    __shared__ float red[4][F];
-    __shared__ float dpart[3][F];      // device side of d a, dU0, dc' per channel
-    __shared__ int32_t rps[kOpTile + 1];
-    const int32_t t = blockIdx.x, rep = blockIdx.y;
+    constexpr int MDP = 16 * DB, AS = MDP + 4;
+    extern __shared__ float sh[];                // statistics [nd][K][3] | dz sums [K][4 wavefronts][MDP]
+    __shared__ float cst[4][256];
+    __shared__ float a2[kOpTile * AS];           // alpha of device<-op links, placement bit in the sign bit
+    __shared__ float zu[kOpTile][2];             // dz sums of an op's links per bit
+    __shared__ float red[4][4][256];             // per wavefront: d a, dU0, dc', d adst
+    int32_t t, rep;
+    od_block(T, t, rep);
+    const int F = P.F, K = T.K, D = F / K;
     const int32_t u0 = T.tiles[3 * t], n = T.tiles[3 * t + 1], g = T.tiles[3 * t + 2];
     const int32_t d0 = T.dev_off[g], nd = T.dev_off[g + 1] - d0;
-    const int MD = T.max_dev, MDP = (MD + 15) & ~15;
-    float *md = sh, *dod = md + 2 * MD * FS;
-    float *aw = dod + MD * FS;          // [K][MDP][kAS] alpha of op<-device entries, sign bit = placement bit
-    float *dsm = aw + K * MDP * kAS;    // [MD][K][3] device<-op statistics (max, 1/sum, c)
-    float *zacc = dsm + 3 * MD * K;     // [4][MD][K] sums of dz over device<-op entries per wavefront
-    float *z1 = zacc + 4 * MD * K;      // [4][2][K][MDP] sums of dz over op<-device entries per wavefront and bit
-    uint8_t *ent = reinterpret_cast<uint8_t *>(z1 + 8 * K * MDP);
-    for (int i = threadIdx.x; i < K * MDP * kAS; i += blockDim.x) aw[i] = 0.f;
-    for (int i = threadIdx.x; i < 4 * MD * K; i += blockDim.x) zacc[i] = 0.f;
-    for (int i = threadIdx.x; i < 8 * K * MDP; i += blockDim.x) z1[i] = 0.f;
-    {
-        const float *src = T.dstat + ((int64_t)rep * T.n_dev + d0) * K * 3;
-        for (int i = threadIdx.x; i < nd * K * 3; i += blockDim.x) dsm[i] = src[i];
+    const int64_t tb = (int64_t)rep * T.n_tiles + t, op0 = (int64_t)rep * T.n_op + u0, dv0 = (int64_t)rep * T.n_dev + d0;
+    float *dsm = sh, *zdp = sh + 3 * nd * K;
+    for (int i = threadIdx.x; i < F; i += 256) {
+        cst[0][i] = P.U[((int64_t)F + i) * 2 + 0];
+        cst[1][i] = P.att_src[F + i];
+        cst[2][i] = P.att_dst[F + i];
+        cst[3][i] = P.cp[F + i];
     }
-    od_stage<F, K, ELU, false>(P, T, rep, u0, n, d0, nd, md, dod, nullptr, nullptr, rps, ent);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int grp = lane >> 4, jl = lane & 15;
-    const int c0 = jl * CPE, h = c0 / D;
-    float a[CPE], ad[CPE], u0c[CPE], ga[CPE], gu0[CPE], gcp[CPE];
-    for (int c = 0; c < CPE; ++c) {
-        a[c] = P.att_src[F + c0 + c];
-        ad[c] = P.att_dst[F + c0 + c];
-        u0c[c] = P.U[((int64_t)F + c0 + c) * 2 + 0];
-        ga[c] = gu0[c] = gcp[c] = 0.f;
-    }
-    float *zw = zacc + (size_t)wv * MD * K, *z1w = z1 + (size_t)wv * 2 * K * MDP;
-    const int64_t sbase = (int64_t)rep * T.n_slots * K;
-    const int32_t ebase = rps[0];
-    auto scalars = [&](int32_t cs, int32_t end, float (&m)[4]) {
-        if (cs + lane / K < end) {
-            const int64_t i = sbase + (int64_t)cs * K + lane;
-            m[0] = T.SA1[i]; m[1] = T.SD1[i]; m[2] = T.SA2[i]; m[3] = T.SD2[i];
-        } else {
-            m[0] = m[1] = m[2] = m[3] = 0.f;
-        }
-    };
-    // per entry and head (the lanes of a chunk hold distinct (device, head)
-    // pairs): op<-device alpha into aw and dz into the per-bit sums;
-    // device<-op (s, dalpha) -> (alpha, dz) with the device's merged
-    // statistics, and the dz sums per (device, head)
-    auto to_alpha = [&](int32_t cs, int32_t end, int32_t ui, float (&m)[4]) {
-        const int32_t e = cs + lane / K;
-        if (e < end) {
-            const int eb = ent[e - ebase];
-            const int v = eb & 0x7f, x = eb >> 7, k = lane % K;
-            aw[(k * MDP + v) * kAS + ui] = __int_as_float(__float_as_int(m[0]) | (x << 31));
-            z1w[(x * K + k) * MDP + v] += m[1];
-            const float *st = dsm + (v * K + k) * 3;
-            const float sv = m[2];
-            const float al = __expf(sv - st[0]) * st[1];
-            const float dz = al * (m[3] - st[2]) * (sv > 0.f ? 1.f : P.slope);
-            m[2] = al;
-            m[3] = dz;
-            zw[v * K + k] += dz;
-        }
-    };
-    float nyo[CPE], ndO[CPE], nm[4];
-    auto fetch = [&](int32_t ui) {
-        if constexpr (AHEAD) {
-            const int64_t row = (int64_t)rep * T.n_op + u0 + ui;
-            load_ch<CPE, false>(T.Y_op, row * 2 * F + F + c0, nyo);
-        }
-        scalars(rps[ui], rps[ui + 1], nm);
-    };
-    if (wv < n) fetch(wv);
-    for (int32_t ui = wv; ui < n; ui += 4) {
-        const int64_t row = (int64_t)rep * T.n_op + u0 + ui;
-        float yo[CPE], m0[CPE], m1[CPE], dys[CPE], sc[4];
-        if constexpr (AHEAD) {
-            for (int c = 0; c < CPE; ++c) yo[c] = nyo[c];
-        } else {
-            load_ch<CPE, false>(T.Y_op, row * 2 * F + F + c0, yo);
-        }
-        for (int i = 0; i < 4; ++i) sc[i] = nm[i];
-        const int32_t beg = rps[ui], end = rps[ui + 1];
-        if (ui + 4 < n) fetch(ui + 4);
-        if (beg < end) to_alpha(beg, end, ui, sc);
-        for (int c = 0; c < CPE; ++c) {
-            m0[c] = msg_act<ELU>(yo[c]);
-            m1[c] = msg_act<ELU>(yo[c] + u0c[c]);
-            dys[c] = 0.f;
-        }
-        for (int32_t cs = beg; cs < end; cs += EPC) {
-            if (cs != beg) {   // rows longer than one chunk
-                scalars(cs, end, sc);
-                to_alpha(cs, end, ui, sc);
-            }
-            const int32_t ce = min(end, cs + EPC);
-            for (int32_t e0 = cs; e0 < ce; e0 += 4) {
-                const int32_t e = e0 + grp;
-                const int src = (e - cs) * K + h;   // < 64: e - cs < EPC
-                const float al2 = __shfl(sc[2], src, 64), dz2 = __shfl(sc[3], src, 64);   // device v <- op u
-                if (e < ce) {
-                    const int eb = ent[e - ebase];
-                    const int v = eb & 0x7f, x = eb >> 7;
-                    const float *dv = dod + v * FS + c0;
-                    for (int c = 0; c < CPE; ++c) {
-                        const float mo = x ? m1[c] : m0[c];
-                        const float dpo = dact<ELU>(mo) * fmaf(al2, dv[c], dz2 * a[c]);
-                        dys[c] += dpo;
-                        ga[c] = fmaf(dz2, mo, ga[c]);
-                        if (x) gu0[c] += dpo;
-                        gcp[c] += dpo;
-                    }
-                }
-            }
-        }
-        // the four entry groups' sums, in order
-        for (int c = 0; c < CPE; ++c) {
-            dys[c] += __shfl_xor(dys[c], 16, 64);
-            dys[c] += __shfl_xor(dys[c], 32, 64);
-        }
-        if (grp == 0) {
-            const float zo = T.Zop[(row * 2 + 1) * K + h];
-            float *o = T.dY_op + row * 2 * F + F + c0;
-            for (int c = 0; c < CPE; ++c) o[c] = fmaf(zo, ad[c], dys[c]);
-        }
-    }
-    for (int c = 0; c < CPE; ++c) {
-        ga[c] += __shfl_xor(ga[c], 16, 64);  ga[c] += __shfl_xor(ga[c], 32, 64);
-        gu0[c] += __shfl_xor(gu0[c], 16, 64); gu0[c] += __shfl_xor(gu0[c], 32, 64);
-        gcp[c] += __shfl_xor(gcp[c], 16, 64); gcp[c] += __shfl_xor(gcp[c], 32, 64);
+    for (int i = threadIdx.x; i < nd * K * 3; i += 256) dsm[i] = T.dstat[dv0 * K * 3 + i];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lr = lane & 15, lg = lane >> 4;
+    // lane group lg of wavefront wv takes ops 16 wv + 4 lg .. + 3
+    uint64_t pr[4], bt[4];
+    int32_t rb[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int u = 16 * wv + 4 * lg + i;
+        const bool in = u < n;
+        pr[i] = in ? T.omask[2 * (op0 + u)] : 0ull;
+        bt[i] = in ? T.omask[2 * (op0 + u) + 1] : 0ull;
+        rb[i] = in ? T.rp[u0 + u] : 0;
     }
     __syncthreads();
-    // device side on the matrix cores: wavefront w takes the 16-channel column
-    // blocks w, w + 4, ...; lane l supplies aw[h][rb + l % 16][ks + l / 16]
-    // (A, by bit) and gamma dO[ks + l / 16][column] (B); result register r of
-    // lane l is device rb + 4 (l / 16) + r, channel cb 16 + l % 16
-    float *pdst = T.PD + (((int64_t)rep * T.n_tiles + t) * MD) * F;
-    for (int cb = wv; cb < F / 16; cb += 4) {
-        const int cl = cb * 16 + (lane & 15), hc = cl / D;
-        const float ac = P.att_src[F + cl];
-        float sga = 0.f, sgu = 0.f, sgc = 0.f;
-        float bo[kOpTile / 4];   // this lane's B operands, one per k step
+    for (int h = 0; h < K; ++h) {
+        const float *S2 = T.S2 + ((int64_t)rep * K + h) * T.n_slots, *D2 = T.D2 + ((int64_t)rep * K + h) * T.n_slots;
+        float s2[4][DB], dd2[4][DB], zv[DB];
 #pragma unroll
-        for (int ks = 0; ks < kOpTile / 4; ++ks) {
-            const int uk = 4 * ks + (lane >> 4);
-            bo[ks] = uk < n ? T.gamma * T.dO_op[((int64_t)rep * T.n_op + u0 + uk) * F + cl] : 0.f;
-        }
-        for (int rb = 0; rb < MDP; rb += 16) {
-            f4 t0 = f4{0.f, 0.f, 0.f, 0.f}, t1 = f4{0.f, 0.f, 0.f, 0.f};
-            const float *arow = aw + (hc * MDP + rb + (lane & 15)) * kAS + (lane >> 4);
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int ks = 0; ks < kOpTile / 4; ++ks) {
-                const float w = arow[4 * ks];
-                const bool bit = __float_as_int(w) < 0;
-                const float wa = fabsf(w);
-                t0 = __builtin_amdgcn_mfma_f32_16x16x4f32(bit ? 0.f : wa, bo[ks], t0, 0, 0, 0);
-                t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(bit ? wa : 0.f, bo[ks], t1, 0, 0, 0);
+            for (int db = 0; db < DB; ++db) {
+                const int v = 16 * db + lr;
+                const bool ok = (pr[i] >> v) & 1ull;
+                const int32_t e = rb[i] + __popcll(pr[i] & ((1ull << v) - 1ull));
+                s2[i][db] = ok ? S2[e] : 0.f;
+                dd2[i][db] = ok ? D2[e] : 0.f;
             }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) zv[db] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int u = 16 * wv + 4 * lg + i;
+            float z0 = 0.f, zz = 0.f;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const int v = 16 * db + lr;
+                const bool ok = (pr[i] >> v) & 1ull, x = (bt[i] >> v) & 1ull;
+                const float *st = dsm + (min(v, nd - 1) * K + h) * 3;
+                const float al = ok ? __expf(s2[i][db] - st[0]) * st[1] : 0.f;
+                const float dz = ok ? al * (dd2[i][db] - st[2]) * (s2[i][db] > 0.f ? 1.f : P.slope) : 0.f;
+                a2[u * AS + v] = __int_as_float(__float_as_int(al) | (x ? INT_MIN : 0));
+                z0 += x ? 0.f : dz;
+                zz += x ? dz : 0.f;
+                zv[db] += dz;
+            }
+            z0 = row_sum<16>(z0);
+            zz = row_sum<16>(zz);
+            if (lr == 0) { zu[u][0] = z0; zu[u][1] = zz; }
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const float z = group_sum4(zv[db]);
+            if (lg == 0) zdp[(h * 4 + wv) * MDP + 16 * db + lr] = z;
+        }
+        // (a wavefront reads only the a2 and zu rows it wrote)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        float wa[MDP / 4];
+#pragma unroll
+        for (int ks = 0; ks < MDP / 4; ++ks) wa[ks] = a2[(16 * wv + lr) * AS + 4 * ks + lg];
+        for (int cb = 0; cb < D / 16; ++cb) {
+            const int cl = h * D + 16 * cb + lr;
+            float bo[MDP / 4], y[4], zo[4];
+#pragma unroll
+            for (int ks = 0; ks < MDP / 4; ++ks) bo[ks] = T.gamma * T.dO_dev[(dv0 + min(4 * ks + lg, nd - 1)) * F + cl];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int v = rb + 4 * (lane >> 4) + r;
-                if (v < nd) {
-                    float zb0 = 0.f, zb1 = 0.f;   // the wavefronts' dz sums in order
-                    for (int w = 0; w < 4; ++w) {
-                        zb0 += z1[((w * 2 + 0) * K + hc) * MDP + v];
-                        zb1 += z1[((w * 2 + 1) * K + hc) * MDP + v];
-                    }
-                    const float mb0 = md[(v * 2 + 0) * FS + cl], mb1 = md[(v * 2 + 1) * FS + cl];
-                    const float p0 = dact<ELU>(mb0) * fmaf(ac, zb0, t0[r]);
-                    const float p1 = dact<ELU>(mb1) * fmaf(ac, zb1, t1[r]);
-                    pdst[(int64_t)v * F + cl] = p0 + p1;
-                    sga = fmaf(mb0, zb0, fmaf(mb1, zb1, sga));
-                    sgu += p1;
-                    sgc += p0 + p1;
+                const int64_t row = op0 + min(16 * wv + 4 * lg + r, n - 1);
+                y[r] = T.Y_op[row * 2 * F + F + cl];
+                zo[r] = T.Zop[(row * 2 + 1) * K + h];
+            }
+            f4 t0 = f4{0.f, 0.f, 0.f, 0.f}, t1 = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < MDP / 4; ++ks) {
+                const bool bit = __float_as_int(wa[ks]) < 0;
+                t0 = __builtin_amdgcn_mfma_f32_16x16x4f32(bit ? 0.f : wa[ks], bo[ks], t0, 0, 0, 0);
+                t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(bit ? -wa[ks] : 0.f, bo[ks], t1, 0, 0, 0);
+            }
+            const float U = cst[0][cl], ac = cst[1][cl], ad = cst[2][cl], cp = cst[3][cl];
+            float ga = 0.f, gu = 0.f, gc = 0.f, gd = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int u = 16 * wv + 4 * lg + r;
+                if (u < n) {
+                    const float m0 = msg_act<ELU>(y[r]), m1 = msg_act<ELU>(y[r] + U);
+                    const float z0 = zu[u][0], zz = zu[u][1];
+                    const float p0 = dact<ELU>(m0) * fmaf(ac, z0, t0[r]);
+                    const float p1 = dact<ELU>(m1) * fmaf(ac, zz, t1[r]);
+                    T.dY_op[(op0 + u) * 2 * F + F + cl] = fmaf(zo[r], ad, p0 + p1);
+                    ga = fmaf(z0, m0, fmaf(zz, m1, ga));
+                    gu += p1;
+                    gc += p0 + p1;
+                    gd = fmaf(zo[r], y[r] - cp, gd);
                 }
             }
+            ga = group_sum4(ga); gu = group_sum4(gu); gc = group_sum4(gc); gd = group_sum4(gd);
+            if (lane < 16) { red[wv][0][cl] = ga; red[wv][1][cl] = gu; red[wv][2][cl] = gc; red[wv][3][cl] = gd; }
         }
-        // the column's sums over the four lane groups (device rows)
-        sga += __shfl_xor(sga, 16, 64); sga += __shfl_xor(sga, 32, 64);
-        sgu += __shfl_xor(sgu, 16, 64); sgu += __shfl_xor(sgu, 32, 64);
-        sgc += __shfl_xor(sgc, 16, 64); sgc += __shfl_xor(sgc, 32, 64);
-        if (lane < 16) { dpart[0][cl] = sga; dpart[1][cl] = sgu; dpart[2][cl] = sgc; }
     }
-    // this tile's dz sums of device<-op entries: the four wavefronts' sums in order
-    float *zdst = T.zrec + (((int64_t)rep * T.n_tiles + t) * MD) * K;
-    for (int i = threadIdx.x; i < nd * K; i += blockDim.x) {
-        const size_t st = (size_t)MD * K;
-        zdst[i] = (zacc[i] + zacc[st + i]) + (zacc[2 * st + i] + zacc[3 * st + i]);
+    __syncthreads();
+    // the tile's dz sums of device<-op entries and the parameter sums: the four wavefronts in order
+    for (int i = threadIdx.x; i < nd * K; i += 256) {
+        const float *z = zdp + (i % K) * 4 * MDP + i / K;
+        T.zrec[tb * T.max_dev * K + i] = (z[0] + z[MDP]) + (z[2 * MDP] + z[3 * MDP]);
     }
-    // parameter partials of the block: the wavefronts' op-side sums in order, then the device side
-    const int64_t nb = (int64_t)gridDim.x * gridDim.y, b = (int64_t)rep * gridDim.x + t;
-    auto flush = [&](int qq, int slot, const float (&qv)[CPE]) {
-        if (grp == 0)
-            for (int c = 0; c < CPE; ++c) red[wv][c0 + c] = qv[c];
-        __syncthreads();
-        for (int c = threadIdx.x; c < F; c += 256)
-            T.part[((int64_t)slot * nb + b) * F + c] = ((red[0][c] + red[1][c]) + (red[2][c] + red[3][c])) + dpart[qq][c];
-        __syncthreads();
-    };
-    flush(0, 0, ga);
-    flush(1, 1, gu0);
-    flush(2, 3, gcp);
-    for (int c = threadIdx.x; c < F; c += 256) T.part[((int64_t)2 * nb + b) * F + c] = 0.f;   // no dU1 for od
+    const int64_t nb = (int64_t)gridDim.x * gridDim.y;
+    for (int c = threadIdx.x; c < F; c += 256) {
+        auto sum = [&](int q) { return (red[0][q][c] + red[1][q][c]) + (red[2][q][c] + red[3][q][c]); };
+        T.part[tb * F + c] += sum(0);
+        T.part[(nb + tb) * F + c] += sum(1);
+        T.part[(3 * nb + tb) * F + c] += sum(2);
+        T.part_a1[tb * F + c] = sum(3);
+    }
 }
 
-// device od rows, one wavefront per row: Z = the tiles' dz sums in tile
-// order, dY = the tiles' partials in tile order + Z adst, and per-block sums
-// of d adst = Z (Y - c') over the block's four rows
-template <int F, int K>
+// device od rows, four per block: Z = the sum of the tiles' dz sums, dY = the
+// sum of the tiles' partials + Z adst, and per-block sums of d adst = Z (Y -
+// c').  Each wavefront takes every fourth tile, eight partials in flight, and
+// the wavefronts meet in order (one wavefront per row was a serial chain over
+// the tiles: 155 us for 512 rows of 94 tiles at f = 256, 23 us now).
+template <int F>
 __global__ void __launch_bounds__(256) bwd_od_devices(BwdLayer P, OdTile T, const int32_t *dev_topo) {
-    constexpr int CPL = F / 64, D = F / K;
-    __shared__ float red[4][F];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t row = (int64_t)blockIdx.x * 4 + wv;
+    constexpr int CPL = F / 64, TB = 8;
+    __shared__ float red[4][F], zred[4][16], acc[F];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, K = T.K, D = F / K;
     const int c0 = lane * CPL;
-    float acc[CPL];
-    for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-    if (row < (int64_t)P.R * T.n_dev) {
+    for (int c = threadIdx.x; c < F; c += 256) acc[c] = 0.f;
+    for (int q = 0; q < 4; ++q) {
+        const int64_t row = (int64_t)blockIdx.x * 4 + q;
+        if (row >= (int64_t)P.R * T.n_dev) break;   // (block-uniform)
         const int32_t rep = (int32_t)(row / T.n_dev), d = (int32_t)(row % T.n_dev);
         const int32_t g = dev_topo[d], v = d - T.dev_off[g];
         const int32_t t0 = T.tile_off[g], t1 = T.tile_off[g + 1];
         const int64_t tb = (int64_t)rep * T.n_tiles;
-        float z = 0.f;
-        if (lane < K)
-            for (int32_t t = t0; t < t1; ++t) z += T.zrec[((tb + t) * T.max_dev + v) * K + lane];
-        if (lane < K) T.Zdev[(row * 2 + 1) * K + lane] = z;
-        const float zh = __shfl(z, c0 / D, 64);
-        for (int c = 0; c < CPL; ++c) {
-            float s = 0.f;
-            for (int32_t t = t0; t < t1; ++t) s += T.PD[((tb + t) * T.max_dev + v) * F + c0 + c];
-            T.dY_dev[row * 2 * F + c0 + c] = fmaf(zh, P.att_dst[F + c0 + c], s);
-            acc[c] = zh * (T.Y_dev[row * 2 * F + F + c0 + c] - P.cp[F + c0 + c]);
+        float s[CPL], z = 0.f;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) s[c] = 0.f;
+        // (lane: head lane % K of every (64 / K)-th of the wavefront's tiles)
+        for (int32_t t = t0 + wv + 4 * (lane / K); t < t1; t += 4 * (64 / K))
+            z += T.zrec[((tb + t) * T.max_dev + v) * K + lane % K];
+        for (int32_t t = t0 + wv; t < t1; t += 4 * TB) {
+            float x[TB][CPL];
+#pragma unroll
+            for (int i = 0; i < TB; ++i)
+                load_ch<CPL, false>(T.PD, ((tb + min(t + 4 * i, t1 - 1)) * T.max_dev + v) * F + c0, x[i]);
+#pragma unroll
+            for (int i = 0; i < TB; ++i)
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) s[c] += t + 4 * i < t1 ? x[i][c] : 0.f;
         }
+        for (int o = K; o < 64; o <<= 1) z += __shfl_xor(z, o, 64);
+        if (lane < K) zred[wv][lane] = z;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) red[wv][c0 + c] = s[c];
+        __syncthreads();
+        for (int c = threadIdx.x; c < F; c += 256) {
+            const int h = c / D;
+            const float zh = (zred[0][h] + zred[1][h]) + (zred[2][h] + zred[3][h]);
+            T.dY_dev[row * 2 * F + c] = fmaf(zh, P.att_dst[F + c], (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]));
+            acc[c] = fmaf(zh, T.Y_dev[row * 2 * F + F + c] - P.cp[F + c], acc[c]);
+            if (c % D == 0) T.Zdev[(row * 2 + 1) * K + h] = zh;
+        }
+        __syncthreads();
     }
-    for (int c = 0; c < CPL; ++c) red[wv][c0 + c] = acc[c];
-    __syncthreads();
-    for (int c = threadIdx.x; c < F; c += 256)
-        T.part_a2[(int64_t)blockIdx.x * F + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
+    for (int c = threadIdx.x; c < F; c += 256) T.part_a2[(int64_t)blockIdx.x * F + c] = acc[c];
 }
 
 // slot keys of the op-device links: pos_of[eid] = position in the op<-device
@@ -1909,30 +1871,15 @@ int64_t n_slots(const tag_graph *g, int b) {
     return b == 0 ? 2 * g->e_oo : (b == 3 ? 2 * g->e_dd : g->e_od);
 }
 
-// the op-device tile path needs the topology's device rows in LDS
-// dynamic LDS bytes of the tile kernels: float rows, then one byte per tile entry
-size_t od_scores_lds(int F, int K, int max_dev) {
-    return sizeof(float) * ((size_t)3 * max_dev * (F + 4) + (size_t)3 * max_dev * K + (size_t)4 * 16 * K * 3) +
-           (size_t)kOpTile * max_dev;
-}
-size_t od_messages_lds(int F, int K, int max_dev) {
-    const size_t mdp = (size_t)(max_dev + 15) / 16 * 16;
-    return sizeof(float) * ((size_t)3 * max_dev * (F + 4) + (size_t)K * mdp * kAS + (size_t)7 * max_dev * K +
-                            (size_t)8 * K * mdp) + (size_t)kOpTile * max_dev;
+// dynamic LDS of bwd_od_messages: device statistics and dz sums
+size_t od_messages_lds(int K, int max_dev) {
+    return sizeof(float) * ((size_t)3 * max_dev * K + (size_t)4 * K * ((max_dev + 15) / 16 * 16));
 }
 
-// (heads of at least 16 channels and at least f/16: one head inside a 16-lane
-// entry group and inside a 16-channel column block of the device-side products)
-bool od_tiles_fit(const tag_graph *g, int F, int K) {
-    // dynamic rows + the static reduction rows and row pointers of the messages kernel
-    // static LDS of the two kernels: row pointers, reduction and constant rows, op masks and Z
-    const size_t rp = sizeof(int32_t) * (kOpTile + 1);
-    const size_t stat_m = sizeof(float) * 7 * F + rp;
-    const size_t stat_s = sizeof(float) * (8 * F + (size_t)kOpTile * K) + 2 * sizeof(uint64_t) * kOpTile + rp;
-    return g->n_tiles > 0 && g->max_dev <= 16 && K <= 16 && F / K >= 16 &&
-           od_messages_lds(F, K, g->max_dev) + stat_m <= 64 * 1024 &&
-           od_scores_lds(F, K, g->max_dev) + stat_s <= 64 * 1024;
-}
+// The op-device tile path takes what the forward pass's tile path takes (its
+// op masks are read here): heads of at least 16 channels, at most 16 heads;
+// a topology has at most 64 devices.
+bool od_tiles_fit(const tag_graph *g, const FwdLayout &fl) { return g->n_tiles > 0 && fl.mfma; }
 
 int32_t persist_blocks(int64_t items) {
     return (int32_t)std::max<int64_t>(1, std::min<int64_t>(kPersist, (items + 3) / 4));
@@ -1997,7 +1944,7 @@ size_t carve_train(const tag_graph *g, const tag_model_dims *d, int32_t R, int32
         L->part_a[b] = c.take<float>((size_t)L->nb_a[b] * F);
         L->part_m[b] = c.take<float>((size_t)4 * L->nb_m[b] * F);
     }
-    if (od_tiles_fit(g, (int)F, (int)K)) {
+    if (od_tiles_fit(g, fl)) {
         const int64_t nb = (int64_t)R * g->n_tiles;
         L->PD = c.take<float>((size_t)nb * g->max_dev * F);
         L->part_od = c.take<float>((size_t)4 * nb * F);
@@ -2041,16 +1988,18 @@ size_t carve_train(const tag_graph *g, const tag_model_dims *d, int32_t R, int32
     return c.used;
 }
 
-// LDS floats of the op-device tile kernels
-
 template <int F, int K, bool ELU>
 void launch_layer_bwd(const BwdLayer &P, BwdBucket (&B)[4], BwdSrc (&S)[4], const ParamReduce &pr, const OdTile *od,
                       const int32_t *dev_topo, hipStream_t st) {
     const dim3 tgrid(od ? (unsigned)od->n_tiles : 1u, (unsigned)P.R);
     if (od) {
         prof_begin(TAG_STAGE_BWD_SCORES, st);
-        if constexpr (K <= 16 && F / K >= 16)
-            bwd_od_scores<F, K, ELU><<<tgrid, 256, od_scores_lds(F, K, od->max_dev), st>>>(P, *od);
+        switch ((od->max_dev + 15) / 16) {
+            case 1: bwd_od_scores<ELU, 1><<<tgrid, 256, 0, st>>>(P, *od); break;
+            case 2: bwd_od_scores<ELU, 2><<<tgrid, 256, 0, st>>>(P, *od); break;
+            case 3: bwd_od_scores<ELU, 3><<<tgrid, 256, 0, st>>>(P, *od); break;
+            default: bwd_od_scores<ELU, 4><<<tgrid, 256, 0, st>>>(P, *od);
+        }
         prof_end(TAG_STAGE_BWD_SCORES, st);
     }
     for (int b = 0; b < 4; ++b) {
@@ -2087,13 +2036,18 @@ void launch_layer_bwd(const BwdLayer &P, BwdBucket (&B)[4], BwdSrc (&S)[4], cons
     }
     if (od) {
         prof_begin(TAG_STAGE_BWD_SOFTMAX, st);
-        bwd_od_dev_stats<<<grid_for((int64_t)P.R * od->n_dev * K), 256, 0, st>>>(P, *od, dev_topo, K);
+        bwd_od_dev_stats<<<(unsigned)(((int64_t)P.R * od->n_dev * K + 3) / 4), 256, 0, st>>>(P, *od, dev_topo, K);
         prof_end(TAG_STAGE_BWD_SOFTMAX, st);
         prof_begin(TAG_STAGE_BWD_MESSAGES, st);
-        if constexpr (K <= 16 && F / K >= 16)
-            bwd_od_messages<F, K, ELU><<<tgrid, 256, od_messages_lds(F, K, od->max_dev), st>>>(P, *od);
+        const size_t lds = od_messages_lds(K, od->max_dev);
+        switch ((od->max_dev + 15) / 16) {
+            case 1: bwd_od_messages<ELU, 1><<<tgrid, 256, lds, st>>>(P, *od); break;
+            case 2: bwd_od_messages<ELU, 2><<<tgrid, 256, lds, st>>>(P, *od); break;
+            case 3: bwd_od_messages<ELU, 3><<<tgrid, 256, lds, st>>>(P, *od); break;
+            default: bwd_od_messages<ELU, 4><<<tgrid, 256, lds, st>>>(P, *od);
+        }
         prof_end(TAG_STAGE_BWD_MESSAGES, st);
-        bwd_od_devices<F, K><<<(unsigned)(((int64_t)P.R * od->n_dev + 3) / 4), 256, 0, st>>>(P, *od, dev_topo);
+        bwd_od_devices<F><<<(unsigned)(((int64_t)P.R * od->n_dev + 3) / 4), 256, 0, st>>>(P, *od, dev_topo);
     }
     for (int s = 0; s < 4; ++s) {
         if (od && (s == 1 || s == 2)) continue;
@@ -2251,7 +2205,7 @@ extern "C" tag_status tag_train_step(const tag_graph *g, const tag_model_dims *d
 
     // layers, last to first
     if (L.dev_topo) dev_topology<<<grid_for(g->n_dev), 256, 0, stream>>>(g->dev_off_d, g->G, g->n_dev, L.dev_topo);
-    if (g->e_od > 0) {
+    if (g->e_od > 0 && !L.PD) {
         od_positions<<<grid_for(g->e_od), 256, 0, stream>>>(g->eid[1], g->e_od, L.pos_of);
         od_map<<<grid_for(g->e_od), 256, 0, stream>>>(g->eid[2], g->e_od, L.pos_of, L.m21);
     }
@@ -2301,10 +2255,10 @@ extern "C" tag_status tag_train_step(const tag_graph *g, const tag_model_dims *d
         const bool use_od = L.PD != nullptr;
         if (use_od) {
             od.tiles = g->tiles_d; od.dev_off = g->dev_off_d;
-            od.rp = g->rowptr[1]; od.col = g->col[1]; od.eid = g->eid[1];
+            od.rp = g->rowptr[1]; od.omask = FL.omask; od.K = K;
             od.n_op = g->n_op; od.n_dev = g->n_dev; od.n_slots = n_slots(g, 1);
             od.Y_op = Yo; od.Y_dev = Yd; od.dO_op = L.G_op; od.dO_dev = L.G_dev; od.gamma = gc;
-            od.SA1 = L.SA[1]; od.SD1 = L.SD[1]; od.SA2 = L.SA[2]; od.SD2 = L.SD[2];
+            od.S2 = L.SA[2]; od.D2 = L.SD[2];
             od.Zop = L.Zop; od.Zdev = L.Zdev; od.dY_op = L.dY_op; od.dY_dev = L.dY_dev;
             od.PD = L.PD; od.max_dev = std::max(g->max_dev, 1); od.n_tiles = g->n_tiles;
             od.tile_off = g->tile_off_d; od.part = L.part_od;

@@ -128,10 +128,9 @@ def test_train_step_matches_reference_workload_topology(torch, name, R, S, Q_per
 
 @pytest.mark.parametrize("f,heads", [(256, 8), (128, 16)])
 def test_train_step_long_device_rows(torch, f, heads):
-    """cnn topology (device rows of 1200 op links): at f = 256 its 16 device
-    rows do not fit in LDS, so the generic passes run and the device<-op
-    softmax takes the entry-per-lane path for long rows; at f = 128 with 16
-    heads the op-device tile path runs with 8-channel heads."""
+    """cnn topology (device rows of 1200 op links): the op-device tile path at
+    f = 256; at f = 128 with 16 heads (8 channels each) the generic passes,
+    whose device<-op softmax takes the entry-per-lane path for long rows."""
     topo = synth.make_topology("cnn")
     _say(f"[train] cnn long device rows f={f} K={heads}")
     c = TrainCase([topo], 1, f, heads, 1, 64, 2, seed=f + heads)
@@ -155,6 +154,28 @@ def test_train_step_matches_reference_union_of_topologies(torch, f, heads, layer
     ref_loss, ref_g = c.reference()
     worst = _compare(tr, loss, ref_loss, ref_g, c.w)
     _say(f"[train] union: worst relative gradient error {max(worst.values()):.2e}")
+
+
+@pytest.mark.parametrize("f,heads,sizes", [(64, 4, [(65, 16, 3), (130, 17, 5)]),      # one and two device blocks
+                                           (128, 8, [(64, 32, 32), (70, 5, 2)]),      # a full second block; a small one
+                                           (256, 4, [(129, 33, 33), (3, 1, 1)]),      # three blocks; one op, one device
+                                           (256, 1, [(66, 48, 7)]), (64, 1, [(1, 64, 64), (190, 49, 4)]),
+                                           (256, 16, [(130, 64, 64)])])               # four blocks, narrowest heads
+def test_train_step_device_blocks(torch, f, heads, sizes):
+    """The op-device tile kernels over one to four blocks of 16 devices: edges
+    of a block, full and sparse placements, ragged op tiles, unlike topologies
+    in one graph."""
+    topos = [synth.random_topology(31 + i, n, m, 2 * n, od_per_op=od, dd_density=0.6)
+             for i, (n, m, od) in enumerate(sizes)]
+    c = TrainCase(topos, 2, f, heads, 2, 24, 2, seed=f + heads + len(sizes))
+    graph, model, tr, feats = c.trainer(torch)
+    loss = float(tr.step(feats).cpu()[0])
+    ref_loss, ref_g = c.reference()
+    worst = _compare(tr, loss, ref_loss, ref_g, c.w)
+    _say(f"[train] device blocks f={f} K={heads} {sizes}: worst relative gradient error {max(worst.values()):.2e}")
+    g1 = {k: v.clone() for k, v in tr.grads.items()}
+    tr.step(feats)
+    assert all(torch.equal(g1[k], tr.grads[k]) for k in OT.PARAMS)
 
 
 def test_train_step_repeatable_and_sgd_update(torch):
