@@ -439,3 +439,27 @@ def test_decide_query_groups(m_dev, f, H, S, scale):
             assert res["argmax"][q] == od["argmax"][0], q
         np.testing.assert_allclose(res["best"][q], od["best"][0], rtol=1e-5, atol=1e-5)
         np.testing.assert_allclose(res["prior"][q], od["prior"][0], rtol=1e-4, atol=1e-7)
+
+
+@pytest.mark.parametrize("f_op,f,dtype", [(1, 64, "f32"), (31, 128, "bf16"), (32, 256, "f32"), (33, 64, "bf16"),
+                                          (42, 128, "f32"), (47, 256, "bf16"), (48, 64, "f32"), (49, 128, "f32"),
+                                          (64, 256, "bf16"), (63, 64, "f32")])
+def test_encoder_feature_widths_many_rows(f_op, f, dtype):
+    """8,241 op rows (a last unit of one row): feature widths at and around the 32-wide steps and the 48-feature
+    weight rows, odd widths (rows 4-byte aligned), 64 to 256 columns."""
+    n, R = 41, 201
+    topo = synth.random_topology(900 + f_op, n, 3, 60)
+    rng = np.random.default_rng((2302, 91, f_op))
+    w = synth.make_weights(f, 4, 1, f_op, f, bias_scale=0.3, seed_extra=f_op)
+    x = [rng.uniform(-1, 1, (R, n, f_op)).astype(np.float32), rng.uniform(-1, 1, (R, 3, 8)).astype(np.float32),
+         rng.uniform(-1, 1, topo.e_oo).astype(np.float32), rng.uniform(-1, 1, (R, topo.e_dd, 2)).astype(np.float32),
+         rng.integers(0, 2, (R, topo.e_od)).astype(np.uint8)]
+    g = P.Graph([topo])
+    m = P.Model(w, f=f, heads=4, layers=1, f_op=f_op, dtype=dtype)
+    E_op, E_dev = P.forward(g, m, *(dev_tensor(a) for a in x))
+    for r in (0, 7, 100, R - 1):
+        R_op, R_dev = oracle.forward(topo, x[0][r], x[1][r], x[2], x[3][r], x[4][r], w, f=f, heads=4, layers=1,
+                                     bf16=dtype == "bf16")
+        got = np.vstack([E_op[r].cpu().numpy(), E_dev[r].cpu().numpy()])
+        assert row_rel_err(got, np.vstack([R_op, R_dev])) <= (2e-2 if dtype == "bf16" else 1e-5), r
+    g.close()
