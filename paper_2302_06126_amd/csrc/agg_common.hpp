@@ -101,21 +101,28 @@ struct AggArgs {
     int32_t rec_mode;                 // 0: records per 256-entry chunk, 1: per tile group
     int32_t n_groups;
     const int32_t *groups, *group_off;   // tile groups of the device<-op blocks
-    // written once per forward pass by prep_tiles_x: per op tile (first op,
+    // written once per forward pass by prep_tiles_x: per op tile part (first op,
     // op count, topology, first op<-op CSR entry, op<-op entries, first
     // device, device count, 0), and the op<-op edge features in CSR order
-    int32_t *tile_ext;                // [n_tiles][8]
+    int32_t *tile_ext;                // [n_tiles * tile_sub][8]
+    int32_t tile_sub;                 // parts an op tile is cut into (1 or 4)
     float *xcsr; int64_t s_xcsr;      // [xrep][nnz of B0], xrep = 1 (shared features) or R
 };
 
-// MFMA path (agg_mfma.hip)
-// whether the tile path takes a layer: heads of 16 to F channels (K <= 16),
+// MFMA path (agg_mfma.hip): whether the tile path takes a layer: heads of 16 to F channels (K <= 16),
 // and the per-candidate transform rows (n_op 2F elements of esz bytes) and
 // the device message table (three parts of R n_dev F words) addressed by
 // 32-bit byte offsets
+// Parts an op tile is cut into for the op destinations (1 or kTileParts).  With
+// few tiles a block's serial chain (prologue loads, four rows per lane group)
+// is the time, not the chip's rate; with more of them the parts repeat the
+// per-block set-up.  Three layers, 1,200 ops, 16 devices, whole | parts, us:
+// 152 tiles 260 | 240 (f = 256), 199 | 171 (128), bf16 230 | 221; 304 tiles
+// 313 | 302, 226 | 210, bf16 263 | 264 (48 devices: 360 | 366); 513 tiles 419 |
+// 400, 251 | 253, bf16 331 | 343; 760 tiles 294 | 303 (128), bf16 385 | 428.
+constexpr int kTileParts = 4;
+inline int op_tile_parts(int64_t n_tiles, int64_t R, bool bf) { return n_tiles * R < (bf ? 256 : 384) ? kTileParts : 1; }
 bool mfma_path_supported(int F, int K, int64_t n_op, int64_t R, int64_t n_dev, int esz);
-void launch_pack_masks(const AggArgs &A, hipStream_t st);
-void launch_prep_tiles_x(const AggArgs &A, int64_t nnz0, hipStream_t st);
 bool launch_agg_mfma(int F, int K, bool bf, const AggArgs &A, hipStream_t st);
 
 // CPL consecutive channels starting at element `off` (fp32 or bf16 storage);

@@ -26,74 +26,10 @@
 namespace tag {
 namespace {
 
-// omask[r][u] = (present, bits) over the local devices of u's topology.
-// One block per (op tile, kMaskCands candidates): the tile's op<-dev CSR range
-// is read once for the group; four lanes per op row walk its entries and OR
-// device bits in registers, and the four partial masks meet by shuffles.
-constexpr int kMaskCands = 4;
-static_assert(kMaskCands == 4 && kOpTile * 4 == 256, "one lane per quarter row and per stored candidate");
-
-__global__ void __launch_bounds__(256) pack_op_masks(AggArgs A) {
-    typedef unsigned long long u64;
-    const int32_t t = blockIdx.x, r0 = blockIdx.y * kMaskCands;
-    const int32_t u0 = A.tiles[3 * t], nu = A.tiles[3 * t + 1], g = A.tiles[3 * t + 2];
-    const int32_t d0 = A.dev_off[g];
-    const int i = threadIdx.x >> 2, q = threadIdx.x & 3;   // op row of the tile, quarter
-    u64 pres = 0ull, bits[kMaskCands];
-#pragma unroll
-    for (int k = 0; k < kMaskCands; ++k) bits[k] = 0ull;
-    if (i < nu) {
-        const int32_t e1 = A.rp[1][u0 + i + 1];
-        for (int32_t e = A.rp[1][u0 + i] + q; e < e1; e += 4) {
-            const u64 m = 1ull << (A.col[1][e] - d0);
-            const int64_t id = A.eid[1][e];
-            pres |= m;
-#pragma unroll
-            for (int k = 0; k < kMaskCands; ++k)
-                if (r0 + k < A.R && A.x_od[(int64_t)(r0 + k) * A.s_od + id]) bits[k] |= m;
-        }
-    }
-    // lanes 4i .. 4i + 3 of one wavefront hold the quarters of row i
-#pragma unroll
-    for (int o = 1; o < 4; o <<= 1) {
-        pres |= __shfl_xor(pres, o);
-#pragma unroll
-        for (int k = 0; k < kMaskCands; ++k) bits[k] |= __shfl_xor(bits[k], o);
-    }
-    if (i < nu && r0 + q < A.R) {   // lane q stores candidate r0 + q
-        u64 b = bits[0];
-#pragma unroll
-        for (int k = 1; k < kMaskCands; ++k) b = q == k ? bits[k] : b;
-        const int64_t mi = 2 * ((int64_t)(r0 + q) * A.n_op + u0 + i);
-        A.omask[mi] = pres;
-        A.omask[mi + 1] = b;
-    }
-}
-
 // Attention terms of node rows when the transform epilogue cannot form them
 // (heads wider than 64 channels): per row, S = (p0, p1, q_od, q_same) and, for
 // device rows, the message table T (bit 0 / 1; fp32, or its exact bf16
 // splits in the bf16 variant).  One wavefront per row.
-// Once per forward pass: the op tiles' descriptors (so an op-destination block
-// finds its CSR range and device group in one load round) and the op<-op
-// edge features in CSR order (so it loads them without the edge-id gather).
-__global__ void __launch_bounds__(256) prep_tiles_x(AggArgs A, int64_t nnz0, int32_t xrep) {
-    const int64_t n = (int64_t)A.n_tiles + (int64_t)xrep * nnz0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        if (i < A.n_tiles) {
-            const int32_t t = (int32_t)i;
-            const int32_t u0 = A.tiles[3 * t], nu = A.tiles[3 * t + 1], g = A.tiles[3 * t + 2];
-            const int32_t eb = A.rp[0][u0], d0 = A.dev_off[g];
-            int32_t *o = A.tile_ext + 8 * (int64_t)t;
-            o[0] = u0; o[1] = nu; o[2] = g; o[3] = eb; o[4] = A.rp[0][u0 + nu] - eb;
-            o[5] = d0; o[6] = A.dev_off[g + 1] - d0; o[7] = 0;
-        } else {
-            const int64_t j = i - A.n_tiles, r = j / nnz0, e = j % nnz0;
-            A.xcsr[j] = A.x_oo[r * A.s_oo + A.eid[0][e]];
-        }
-    }
-}
-
 template <int F, int K, bool BF, bool ELU = false>
 __global__ void __launch_bounds__(256) prep_rows(AggArgs A, int dev_side) {
     constexpr int CPL = F / 64, LPH = 64 / K;
@@ -433,7 +369,8 @@ __global__ void __launch_bounds__(256) agg_b2(AggArgs A) {
         }
 }
 
-// Op destinations of one 64-op tile of one candidate.
+// Op destinations of one op tile of one candidate: TR = 64 rows, or 16 (a part
+// of a tile) where the tiles alone leave CUs idle (see op_tile_parts).
 //  * op <- op: each 16-lane group streams the entries of four consecutive
 //    tile rows (one contiguous CSR range, staged in LDS as (source, edge
 //    feature) pairs, ECAP at a time) with EB neighbour rows always in
@@ -445,7 +382,7 @@ __global__ void __launch_bounds__(256) agg_b2(AggArgs A) {
 //  * op <- device: MFMA contraction of the attention weights (formed in
 //    registers) with the device message table.
 // Both parts are combined and each op row is written once.
-template <int F, int K, bool BF, bool ELU = false>
+template <int F, int K, bool BF, bool ELU, int TR>
 __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile(AggArgs A) {
     constexpr int D = F / K;
     constexpr int WC = F / 4;
@@ -456,23 +393,25 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
     constexpr int LPH = 16 / K;              // op<-op lanes per head (K <= 16 on this path)
     // neighbour rows in flight per 16-lane group (a slot holds CPL or CPL/2 words)
     constexpr int EB = BF ? (F >= 256 && K >= 8 ? 4 : 8) : (F >= 256 ? 2 : 4);
+    constexpr int RPG = TR / 16;             // rows per 16-lane group
+    constexpr int NB2 = TR >= 32 ? 2 : 1;    // op<-device row blocks per pass
     constexpr int OS = F + 4;                // LDS tile row stride
-    constexpr int ECAP = F >= 256 ? 512 : 192;   // op<-op entries staged in LDS per chunk (192 keeps
+    constexpr int ECAP = TR < kOpTile ? 128 : F >= 256 ? 512 : 192;   // op<-op entries staged in LDS per chunk (192 keeps
                                                  // four blocks per CU at f = 128)
-    __shared__ __attribute__((aligned(16))) float Ot[kOpTile * OS];
-    __shared__ uint64_t pres[kOpTile], bits[kOpTile];
-    __shared__ float qo[kOpTile][K], mxS[kOpTile][K];
+    __shared__ __attribute__((aligned(16))) float Ot[TR * OS];
+    __shared__ uint64_t pres[TR], bits[TR];
+    __shared__ float qo[TR][K], mxS[TR][K];
     // op<-op destination terms: staged per tile row where the LDS budget
     // allows (f = 256); smaller f keeps the group's four rows in registers
     // (four blocks per CU at f = 128 leave no room for the array)
     constexpr bool kQL = F >= 256;
-    __shared__ float qoo[kQL ? kOpTile : 1][kQL ? K : 1];
+    __shared__ float qoo[kQL ? TR : 1][kQL ? K : 1];
     // op<-op per-channel constants (a log2 e, U_0, c') staged once per block
     // where the LDS budget allows (f = 256); smaller f loads them per lane
     constexpr bool kCS = F >= 256;
     __shared__ __attribute__((aligned(16))) float CA[kCS ? 3 : 1][kCS ? F : 4];
     __shared__ float P[64][2][K];
-    __shared__ int32_t Erp[kOpTile + 1];
+    __shared__ int32_t Erp[TR + 1];
     __shared__ int2 Ecx[ECAP];             // staged entries: (source op, edge feature bits)
     __shared__ uint8_t Erw[ECAP];          // tile row of each staged entry
 
@@ -486,6 +425,7 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
     const int4 te0 = *reinterpret_cast<const int4 *>(A.tile_ext + 8 * (int64_t)t);
     const int4 te1 = *reinterpret_cast<const int4 *>(A.tile_ext + 8 * (int64_t)t + 4);
     const int32_t u0 = te0.x, nu = te0.y;
+    if (TR < kOpTile && nu == 0) return;   // a part past a short tile's end
     const int32_t d0 = te1.y, Mg = te1.z;
     const float *xc = A.xcsr + (int64_t)r * A.s_xcsr;   // op<-op edge features in CSR order
     const float *Sop = A.Sop + (int64_t)r * A.n_op * 4 * K;
@@ -495,11 +435,11 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
 
     // this lane's op<-op channels c0 .. c0+CPL-1 of the group's four rows
     const int c0 = (lane & 15) * CPL;
-    const int gr0 = wave * 16 + (lane >> 4) * 4;   // the group's first tile row
-    float qv[4];                                   // (kQL false) the group's op<-op destination terms
+    const int gr0 = (tid >> 4) * RPG;   // the group's first tile row
+    float qv[RPG];                                 // (kQL false) the group's op<-op destination terms
     if constexpr (!kQL) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < RPG; ++i)
             qv[i] = gr0 + i < nu ? Sop[(int64_t)(u0 + gr0 + i) * 4 * K + 3 * K + c0 / D] : 0.f;
     }
     float a[CPL], u0c[CPL], cpc[CPL];
@@ -517,7 +457,7 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
     const int32_t ntot = te1.x;                    // the tile's op<-op entries: one CSR range
     const int32_t ne = min(ntot, ECAP);
     {
-        constexpr int NQ = (kOpTile * K + 255) / 256, NP = (64 * 2 * K + 255) / 256, NE = (ECAP + 255) / 256;
+        constexpr int NQ = (TR * K + 255) / 256, NP = (64 * 2 * K + 255) / 256, NE = (ECAP + 255) / 256;
         int32_t rp0 = 0, rp1 = 0;
         uint64_t om0 = 0, om1 = 0;
         float q2v[NQ], q3v[NQ], pv[NP], exv[NE];
@@ -532,7 +472,7 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
 #pragma unroll
         for (int k = 0; k < NQ; ++k) {
             const int i = tid + 256 * k, u = i / K, h = i % K;
-            const bool ok = i < kOpTile * K && u < nu;
+            const bool ok = i < TR * K && u < nu;
             q2v[k] = ok ? Sop[(int64_t)(u0 + u) * 4 * K + 2 * K + h] : 0.f;   // op <- device
             q3v[k] = kQL && ok ? Sop[(int64_t)(u0 + u) * 4 * K + 3 * K + h] : 0.f;   // op <- op
         }
@@ -548,11 +488,11 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
             exv[k] = i < ne ? xc[eb + i] : 0.f;
         }
         if (tid <= nu) Erp[tid] = rp0;
-        if (tid < kOpTile) { pres[tid] = om0; bits[tid] = om1; }
+        if (tid < TR) { pres[tid] = om0; bits[tid] = om1; }
 #pragma unroll
         for (int k = 0; k < NQ; ++k) {
             const int i = tid + 256 * k;
-            if (i < kOpTile * K) {
+            if (i < TR * K) {
                 qo[i / K][i % K] = q2v[k] * kLog2e;
                 if constexpr (kQL) qoo[i / K][i % K] = q3v[k] * kLog2e;
             }
@@ -576,7 +516,7 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
     }
     __syncthreads();
     // op <- device softmax maxima (LeakyReLU of the largest pre-activation)
-    for (int i = tid; i < kOpTile * K; i += 256) {
+    for (int i = tid; i < TR * K; i += 256) {
         const int u = i / K, h = i % K;
         uint64_t pr = pres[u];
         const uint64_t bt = bits[u];
@@ -620,13 +560,13 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
             }
         }
         // the group's entries (rows >= nu are empty)
-        const int32_t ebeg = Erp[min(gr0, nu)], eend = Erp[min(gr0 + 4, nu)];
+        const int32_t ebeg = Erp[min(gr0, nu)], eend = Erp[min(gr0 + RPG, nu)];
         if constexpr (!kQL) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) qv[i] *= kLog2e;
+            for (int i = 0; i < RPG; ++i) qv[i] *= kLog2e;
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < RPG; ++i)
             if (gr0 + i < nu)
                 for (int c = 0; c < CPL; ++c) Ot[(gr0 + i) * OS + c0 + c] = 0.f;   // rows without entries stay zero
         const float gs = A.g_same;
@@ -683,6 +623,7 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
                 }
                 float qd;   // the destination term of row rl
                 if constexpr (kQL) qd = qoo[rl][hd];
+                else if constexpr (RPG == 1) qd = qv[0];
                 else {
                     const int i = rl - gr0;
                     const float qa = (i & 1) ? qv[1] : qv[0], qb = (i & 1) ? qv[3] : qv[2];
@@ -776,13 +717,13 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
         if (ksteps > 0) load_b(0, 0, bops[0]);
         __syncthreads();
 #pragma unroll 1
-        for (int half = 0; half < 2; ++half) {
-            f4 acc[2][NCB];
-            float zl[2][HPW], q2[2][HPW], m2[2][HPW];
-            uint64_t prs[2], bts[2];
+        for (int half = 0; half < TR / 16 / NB2; ++half) {
+            f4 acc[NB2][NCB];
+            float zl[NB2][HPW], q2[NB2][HPW], m2[NB2][HPW];
+            uint64_t prs[NB2], bts[NB2];
 #pragma unroll
-            for (int b2 = 0; b2 < 2; ++b2) {
-                const int u = (2 * half + b2) * 16 + (lane & 15);
+            for (int b2 = 0; b2 < NB2; ++b2) {
+                const int u = (NB2 * half + b2) * 16 + (lane & 15);
                 prs[b2] = pres[u];
                 bts[b2] = bits[u];
 #pragma unroll
@@ -797,10 +738,10 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
 #pragma unroll 1
             for (int ks = 0; ks < ksteps; ++ks) {
                 const int jb = 32 * ks + 8 * (lane >> 4);
-                unsigned on8[2], bit8[2];
-                int idx[2];
+                unsigned on8[NB2], bit8[NB2];
+                int idx[NB2];
 #pragma unroll
-                for (int b2 = 0; b2 < 2; ++b2) {
+                for (int b2 = 0; b2 < NB2; ++b2) {
                     // the lane's eight presence and bit flags (never set for jb + q >= Mg)
                     on8[b2] = (unsigned)(prs[b2] >> jb) & 0xffu;
                     bit8[b2] = (unsigned)(bts[b2] >> jb) & 0xffu;
@@ -818,9 +759,9 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
                         p0q[q] = P[jb + q][0][h0 + hh];
                         p1q[q] = P[jb + q][1][h0 + hh];
                     }
-                    bf8 aop[2][3];
+                    bf8 aop[NB2][3];
 #pragma unroll
-                    for (int b2 = 0; b2 < 2; ++b2) {
+                    for (int b2 = 0; b2 < NB2; ++b2) {
                         unsigned w[3][4];
 #pragma unroll
                         for (int pr = 0; pr < 4; ++pr) {
@@ -854,12 +795,12 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
                         auto prefetch = [&]() {
                             if (cb + 1 < NCB) load_b(ks, cb + 1, bops[(cb + 1) & 1]);
                             else if (ks + 1 < ksteps) load_b(ks + 1, 0, bops[0]);
-                            else if (half == 0) load_b(0, 0, bops[0]);
+                            else if (half + 1 < TR / 16 / NB2) load_b(0, 0, bops[0]);
                         };
                         constexpr bool kAlt = NCB % 2 == 0;   // consecutive pairs alternate buffers
                         if (kAlt || cb + 1 < NCB) prefetch();
 #pragma unroll
-                        for (int b2 = 0; b2 < 2; ++b2)
+                        for (int b2 = 0; b2 < NB2; ++b2)
                             acc[b2][cb] = smfmac_split3(aop[b2], bops[cb & 1], idx[b2], acc[b2][cb]);
                         if (!kAlt && cb + 1 == NCB) prefetch();
                     }
@@ -870,8 +811,8 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
             // rb*16 + 4(l/16) + v; the op<-device part is added into the LDS
             // tile in place (each (row, column) belongs to one lane)
 #pragma unroll
-            for (int b2 = 0; b2 < 2; ++b2) {
-                const int rb = 2 * half + b2;
+            for (int b2 = 0; b2 < NB2; ++b2) {
+                const int rb = NB2 * half + b2;
                 float scale[HPW][4];
 #pragma unroll
                 for (int hh = 0; hh < HPW; ++hh) {
@@ -903,10 +844,10 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
         // the sparse products at two); the table loads of SB steps are issued
         // together
         constexpr int SB = 4;
-        f4 acc[4][NCB];
-        float zl[4][HPW];
+        f4 acc[TR / 16][NCB];
+        float zl[TR / 16][HPW];
 #pragma unroll
-        for (int rb = 0; rb < 4; ++rb) {
+        for (int rb = 0; rb < TR / 16; ++rb) {
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) acc[rb][cb] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -928,10 +869,10 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
         load_batch(0);
         __syncthreads();
         // per-lane constants of the lane's op rows u = rb*16 + l%16
-        uint64_t prs[4], bts[4];
-        float q2[4][HPW], m2[4][HPW];
+        uint64_t prs[TR / 16], bts[TR / 16];
+        float q2[TR / 16][HPW], m2[TR / 16][HPW];
 #pragma unroll
-        for (int rb = 0; rb < 4; ++rb) {
+        for (int rb = 0; rb < TR / 16; ++rb) {
             const int u = rb * 16 + (lane & 15);
             prs[rb] = pres[u];
             bts[rb] = bits[u];
@@ -957,7 +898,7 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
 #pragma unroll
                 for (int hh = 0; hh < HPW; ++hh) pj[hh] = P[j][b][h0 + hh];
 #pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
+                for (int rb = 0; rb < TR / 16; ++rb) {
                     const bool on = jok && ((prs[rb] >> j) & 1ull) && ((int)((bts[rb] >> j) & 1ull) == b);
 #pragma unroll
                     for (int hh = 0; hh < HPW; ++hh) {
@@ -976,7 +917,7 @@ __global__ void __launch_bounds__(256, (F >= 256 && K >= 8) ? 1 : 2) agg_op_tile
         // softmax sums of op row rb*16 + l%16 are spread over lanes l, l+16,
         // l+32, l+48; the output row of register v in lane l is rb*16 + 4(l/16) + v
 #pragma unroll
-        for (int rb = 0; rb < 4; ++rb) {
+        for (int rb = 0; rb < TR / 16; ++rb) {
             float scale[HPW][4];
 #pragma unroll
             for (int hh = 0; hh < HPW; ++hh) {
@@ -1026,7 +967,7 @@ template <int F, int K, bool BF, bool ELU = false>
 void launch_mfma(const AggArgs &A, hipStream_t st) {
     const int64_t op_waves = (int64_t)A.R * A.n_op;
     const int64_t dev_waves = (int64_t)A.R * A.n_dev;
-    const dim3 tiles((unsigned)A.n_tiles, (unsigned)A.R);
+    const dim3 tiles((unsigned)(A.n_tiles * A.tile_sub), (unsigned)A.R);
     const dim3 groups((unsigned)A.n_groups, (unsigned)A.R);
     if (!A.prep_done) {
         prof_begin(TAG_STAGE_DEV_PREP, st);
@@ -1038,7 +979,8 @@ void launch_mfma(const AggArgs &A, hipStream_t st) {
     agg_b2<F, K, BF, ELU><<<groups, 256, 0, st>>>(A);
     prof_end(TAG_STAGE_AGG_DEV_OP, st);
     prof_begin(TAG_STAGE_AGG_OP_DEV, st);
-    agg_op_tile<F, K, BF, ELU><<<tiles, 256, 0, st>>>(A);
+    if (A.tile_sub > 1) agg_op_tile<F, K, BF, ELU, kOpTile / kTileParts><<<tiles, 256, 0, st>>>(A);
+    else agg_op_tile<F, K, BF, ELU, kOpTile><<<tiles, 256, 0, st>>>(A);
     prof_end(TAG_STAGE_AGG_OP_DEV, st);
 }
 
@@ -1061,18 +1003,6 @@ bool dispatch_mfma_heads(int K, const AggArgs &A, hipStream_t st) {
 bool mfma_path_supported(int F, int K, int64_t n_op, int64_t R, int64_t n_dev, int esz) {
     return K >= 1 && F / K >= 16 && K <= 16 && n_op * 2 * F * esz < (int64_t(1) << 32) &&
            R * n_dev * F * 12 < (int64_t(1) << 32);
-}
-
-void launch_prep_tiles_x(const AggArgs &A, int64_t nnz0, hipStream_t st) {
-    const int32_t xrep = A.s_xcsr ? A.R : 1;
-    const int64_t n = (int64_t)A.n_tiles + (int64_t)xrep * nnz0;
-    if (n == 0) return;
-    const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
-    prep_tiles_x<<<blocks, 256, 0, st>>>(A, nnz0, xrep);
-}
-
-void launch_pack_masks(const AggArgs &A, hipStream_t st) {
-    pack_op_masks<<<dim3((unsigned)A.n_tiles, (unsigned)((A.R + kMaskCands - 1) / kMaskCands)), 256, 0, st>>>(A);
 }
 
 bool launch_agg_mfma(int F, int K, bool bf, const AggArgs &A, hipStream_t st) {

@@ -21,8 +21,9 @@
 //    fixed order, so results do not depend on scheduling.
 #include <algorithm>
 
-#include "agg_common.hpp"
+#include "agg_prep.hpp"
 #include "fwd_internal.hpp"
+#include "gemm_small.hpp"
 #include "transform.hpp"
 
 namespace tag {
@@ -38,14 +39,14 @@ struct FoldArgs {
 };
 
 // one wavefront per (layer, relation, output channel); lanes split the k sum
-__global__ void __launch_bounds__(64) fold_edge_terms(FoldArgs a) {
+__device__ __forceinline__ void fold_edge_terms(const FoldArgs &a, int item, int lane) {
     const int F = a.F;
-    const int lr = blockIdx.x / F, c = blockIdx.x % F;   // lr = l*3 + r
+    const int lr = item / F, c = item % F;   // lr = l*3 + r
     const int r = lr % 3;
     const int d = (r == 2) ? 2 : 1;
     const float *W = a.layer_w + (size_t)lr * F * 2 * F + (size_t)c * 2 * F + F;   // row c of W^e
     float u0 = 0.f, u1 = 0.f, s = 0.f;
-    for (int k = threadIdx.x; k < F; k += 64) {
+    for (int k = lane; k < F; k += 64) {
         const float we = W[k];
         u0 = fmaf(we, a.A[r][(size_t)k * d + 0], u0);
         if (d == 2) u1 = fmaf(we, a.A[r][(size_t)k * d + 1], u1);
@@ -56,7 +57,7 @@ __global__ void __launch_bounds__(64) fold_edge_terms(FoldArgs a) {
         u1 += __shfl_xor(u1, o, 64);
         s += __shfl_xor(s, o, 64);
     }
-    if (threadIdx.x == 0) {
+    if (lane == 0) {
         a.U[((size_t)lr * F + c) * 2 + 0] = u0;
         a.U[((size_t)lr * F + c) * 2 + 1] = u1;
         a.cp[(size_t)lr * F + c] = a.layer_b[(size_t)lr * F + c] + s;
@@ -64,14 +65,56 @@ __global__ void __launch_bounds__(64) fold_edge_terms(FoldArgs a) {
 }
 
 // W^h of every (layer, relation) to bf16: Wb[l][r][n][k] = bf16(W[l][r][n][k]), k < F
-__global__ void convert_wh_bf16(const float *layer_w, uint16_t *Wb, int F, int LR) {
+__device__ __forceinline__ void convert_wh_bf16(const float *layer_w, uint16_t *Wb, int F, int LR, int64_t i0,
+                                                int64_t stride) {
     int64_t total = (int64_t)LR * F * F;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t i = i0; i < total; i += stride) {
         int64_t lr = i / ((int64_t)F * F);
         int64_t rem = i % ((int64_t)F * F);
         int64_t n = rem / F, k = rem % F;
         Wb[i] = f2bf(layer_w[(lr * F + n) * 2 * F + k]);
+    }
+}
+
+// Everything a forward pass prepares that depends on its inputs alone, in one
+// launch of 256-thread blocks (runs of blocks per part): the node encoders of
+// few rows, the folded edge terms, the bf16 weights, the op placement masks,
+// the tile descriptors and the op<-op features in CSR order.  As launches of
+// their own (up to six of 2 to 6 us each) they took 15 us of a 110 us call on a
+// 200-op graph, together 6.8 us.
+struct Prologue {
+    SmallGemm enc[2];
+    int vec[2];
+    FoldArgs fold;
+    int n_fold;                       // wavefronts' worth of fold items
+    uint16_t *Wb;
+    AggArgs A;
+    int64_t nnz0;
+    int32_t xrep;
+    uint32_t end[6];                  // last block + 1 of each part
+};
+
+__global__ void __launch_bounds__(256) fwd_prologue(Prologue p) {
+    __shared__ __align__(16) float lds[sgemm::Tile<sgemm::kFewM, sgemm::kFewK, 1>::LDS];
+    const uint32_t b = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (b < p.end[1]) {
+        const int side = b < p.end[0] ? 0 : 1;
+        const SmallGemm &G = p.enc[side];
+        const uint32_t i = b - (side ? p.end[0] : 0), nc = (uint32_t)(G.N + sgemm::SN - 1) / sgemm::SN;
+        sgemm::block<sgemm::kFewM, sgemm::kFewK, 1>(G, p.vec[side], i / nc, i % nc, lds, [](int64_t m) { return (int32_t)m; });
+    } else if (b < p.end[2]) {
+        const int item = (int)(b - p.end[1]) * 4 + wave;
+        if (item < p.n_fold) fold_edge_terms(p.fold, item, lane);
+    } else if (b < p.end[3]) {
+        convert_wh_bf16(p.fold.layer_w, p.Wb, p.fold.F, p.n_fold / p.fold.F, (int64_t)(b - p.end[2]) * 256 + threadIdx.x,
+                        (int64_t)(p.end[3] - p.end[2]) * 256);
+    } else if (b < p.end[4]) {
+        const uint32_t i = b - p.end[3];
+        pack_op_masks(p.A, (int32_t)(i % p.A.n_tiles), (int32_t)(i / p.A.n_tiles) * kMaskCands);
+    } else {
+        prep_tiles_x(p.A, p.nnz0, p.xrep, (int64_t)(b - p.end[4]) * 256 + threadIdx.x,
+                     (int64_t)(p.end[5] - p.end[4]) * 256);
     }
 }
 
@@ -373,6 +416,7 @@ size_t carve_fwd(const tag_graph *g, const tag_model_dims *d, int32_t R, void *b
     }
     L->Y_op = c.take<char>((size_t)R * g->n_op * 2 * F * es);
     L->Y_dev = c.take<char>((size_t)R * g->n_dev * 2 * F * es);
+    L->tile_sub = op_tile_parts(g->n_tiles, R, d->dtype == TAG_BF16);
     L->mfma = mfma_path_supported(F, d->heads, g->n_op, R, g->n_dev, (int)es);
     L->maxc = L->mfma ? std::max<int32_t>(1, g->max_groups)
                       : std::max<int32_t>(1, (g->max_degree[2] + kChunk - 1) / kChunk);
@@ -383,7 +427,7 @@ size_t carve_fwd(const tag_graph *g, const tag_model_dims *d, int32_t R, void *b
         // fp32 message table [R n_dev][2][F], or its three bf16 split parts [3][R n_dev][F]
         L->T = c.take<float>((size_t)R * g->n_dev * 3 * F);
         L->Sop = c.take<float>((size_t)R * g->n_op * 4 * d->heads);
-        L->tile_ext = c.take<int32_t>((size_t)std::max<int32_t>(g->n_tiles, 1) * 8);
+        L->tile_ext = c.take<int32_t>((size_t)std::max<int32_t>(g->n_tiles, 1) * L->tile_sub * 8);
         L->xcsr = c.take<float>((size_t)R * std::max<int64_t>(g->nnz[0], 1));
     } else {
         L->omask = nullptr;
@@ -504,22 +548,6 @@ tag_status forward_run(const tag_graph *g, const tag_model_dims *dims, const tag
 
     FoldArgs fa{w->layer_w, w->layer_b, {w->enc_edge_w[0], w->enc_edge_w[1], w->enc_edge_w[2]},
                 {w->enc_edge_b[0], w->enc_edge_b[1], w->enc_edge_b[2]}, L.U, L.cp, F};
-    fold_edge_terms<<<NL * 3 * F, 64, 0, stream>>>(fa);
-    if (bf) convert_wh_bf16<<<256, 256, 0, stream>>>(w->layer_w, L.Wb, F, NL * 3);
-
-    // encoders: hidden h0 in the working precision
-    const int64_t rows_op = (int64_t)R * g->n_op, rows_dev = (int64_t)R * g->n_dev;
-    {
-        // h0 = ReLU(A x + c) as a small-K MFMA GEMM per node type
-        SmallGemm eo{x->x_op, dims->f_op, rows_op, nullptr, dims->f_op, w->enc_op_w, dims->f_op, F,
-                     w->enc_op_b, 1, h_op(0), F, bf ? 1 : 0};
-        SmallGemm ed{x->x_dev, dims->f_dev, rows_dev, nullptr, dims->f_dev, w->enc_dev_w, dims->f_dev, F,
-                     w->enc_dev_b, 1, h_dev(0), F, bf ? 1 : 0};
-        prof_begin(TAG_STAGE_ENCODE, stream);
-        launch_small_gemm(eo, stream);
-        launch_small_gemm(ed, stream);
-        prof_end(TAG_STAGE_ENCODE, stream);
-    }
     AggArgs A{};
     A.R = R;
     A.n_op = g->n_op; A.n_dev = g->n_dev;
@@ -539,9 +567,38 @@ tag_status forward_run(const tag_graph *g, const tag_model_dims *dims, const tag
     A.tile_ext = L.tile_ext;
     A.xcsr = L.xcsr;
     A.s_xcsr = x->stride_oo ? g->nnz[0] : 0;
-    if (L.mfma) {
-        launch_pack_masks(A, stream);
-        launch_prep_tiles_x(A, g->nnz[0], stream);
+    A.tile_sub = L.tile_sub;
+    // encoders h0 = ReLU(A x + c) in the working precision (those of many rows
+    // in launches of their own), and the rest of the prologue
+    {
+        const int64_t rows_op = (int64_t)R * g->n_op, rows_dev = (int64_t)R * g->n_dev;
+        Prologue p{};
+        p.enc[0] = SmallGemm{x->x_op, dims->f_op, rows_op, nullptr, dims->f_op, w->enc_op_w, dims->f_op, F,
+                             w->enc_op_b, 1, h_op(0), F, bf ? 1 : 0};
+        p.enc[1] = SmallGemm{x->x_dev, dims->f_dev, rows_dev, nullptr, dims->f_dev, w->enc_dev_w, dims->f_dev, F,
+                             w->enc_dev_b, 1, h_dev(0), F, bf ? 1 : 0};
+        p.fold = fa;
+        p.n_fold = NL * 3 * F;
+        p.Wb = L.Wb;
+        p.A = A;
+        p.nnz0 = g->nnz[0];
+        p.xrep = A.s_xcsr ? R : 1;
+        uint32_t n = 0;
+        prof_begin(TAG_STAGE_ENCODE, stream);
+        for (int s = 0; s < 2; ++s) {
+            const SmallGemm &e = p.enc[s];
+            p.vec[s] = sgemm::vec_ok(e);
+            if (small_gemm_few(e)) n += (uint32_t)((e.rows + sgemm::kFewM - 1) / sgemm::kFewM * ((F + sgemm::SN - 1) / sgemm::SN));
+            else launch_small_gemm(e, stream);
+            p.end[s] = n;
+        }
+        p.end[2] = n += (uint32_t)(p.n_fold + 3) / 4;
+        p.end[3] = n += bf ? 256u : 0u;
+        p.end[4] = n += L.mfma ? (uint32_t)((int64_t)g->n_tiles * ((R + kMaskCands - 1) / kMaskCands)) : 0u;
+        const int64_t items = (int64_t)g->n_tiles * L.tile_sub + (int64_t)p.xrep * p.nnz0;
+        p.end[5] = n += L.mfma ? (uint32_t)std::min<int64_t>((items + 255) / 256, 4096) : 0u;
+        fwd_prologue<<<n, 256, 0, stream>>>(p);
+        prof_end(TAG_STAGE_ENCODE, stream);
     }
 
     // the transform epilogue forms the attention terms when a head fits one

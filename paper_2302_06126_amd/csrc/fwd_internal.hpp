@@ -16,7 +16,8 @@ struct FwdLayout {
     bool mfma;
     uint64_t *omask;
     float *Sdev, *T, *Sop;
-    int32_t *tile_ext;             // per op tile descriptors (see AggArgs)
+    int32_t *tile_ext;             // op tile descriptors (see AggArgs)
+    int32_t tile_sub;              // parts an op tile is cut into for the op destinations
     float *xcsr;                   // op<-op edge features in CSR order
 };
 

@@ -109,6 +109,7 @@ struct SmallGemm {
     int c_bf16;
 };
 void launch_small_gemm(const SmallGemm &G, hipStream_t st);
+bool small_gemm_few(const SmallGemm &G);   // takes the 16-row blocks of few rows
 
 // C[m][n] (+)= act(bias[n] + sum_k a(m, k) b(n, k)) over exact bf16 splits of
 // fp32 operands (gemm_split.hip): a(m, k) = A[row(m)][k] (a_kc) or A[k][m],

@@ -463,3 +463,34 @@ def test_encoder_feature_widths_many_rows(f_op, f, dtype):
         got = np.vstack([E_op[r].cpu().numpy(), E_dev[r].cpu().numpy()])
         assert row_rel_err(got, np.vstack([R_op, R_dev])) <= (2e-2 if dtype == "bf16" else 1e-5), r
     g.close()
+
+
+@pytest.mark.parametrize("f,heads,dtype,sigma", [(64, 1, "f32", "relu"), (64, 4, "bf16", "relu"), (64, 2, "f32", "elu"),
+                                                 (128, 2, "bf16", "relu"), (128, 8, "f32", "elu"),
+                                                 (256, 16, "f32", "relu"), (256, 4, "bf16", "relu"),
+                                                 (256, 1, "bf16", "relu"), (256, 2, "f32", "elu")])
+def test_op_tile_parts_and_whole_tiles(f, heads, dtype, sigma):
+    """65 ops (a tile of 64, one of one op): two replicas take 16-row parts of the tiles, 200 take whole tiles; a
+    hub op with more links than a part stages at a time.  Both against the oracle, and the replicas they share
+    against each other to the encoders' rounding."""
+    n, m, R = 65, 5, 200
+    rng = np.random.default_rng((2302, 92, f, heads))
+    topo = mk_topo(n, m, oo=[(i, i + 1) for i in range(n - 1)] + [(3, j) for j in range(5, n)] +
+                   [(j, 60) for j in range(4, 59)] + [(i, i + 7) for i in range(8, 50)],
+                   dd=[(0, 1), (1, 4)], od=[(u, j) for u in range(n) for j in range(m) if (u * j) % 3 != 1])
+    w = synth.make_weights(f, heads, 2, 42, f, bias_scale=0.2, seed_extra=f + heads)
+    x = [rng.uniform(-1, 1, (R, n, 42)).astype(np.float32), rng.uniform(-1, 1, (R, m, 8)).astype(np.float32),
+         rng.uniform(-1, 1, (R, topo.e_oo)).astype(np.float32), rng.uniform(-1, 1, (R, topo.e_dd, 2)).astype(np.float32),
+         rng.integers(0, 2, (R, topo.e_od)).astype(np.uint8)]
+    g = P.Graph([topo])
+    mod = P.Model(w, f=f, heads=heads, layers=2, f_op=42, dtype=dtype, sigma=sigma)
+    out = {k: [e.cpu().numpy() for e in P.forward(g, mod, *(dev_tensor(a[:k]) for a in x))] for k in (2, R)}
+    tol = 2e-2 if dtype == "bf16" else 1e-5
+    for r, k in ((0, 2), (1, 2), (0, R), (1, R), (77, R), (R - 1, R)):
+        R_op, R_dev = oracle.forward(topo, x[0][r], x[1][r], x[2][r], x[3][r], x[4][r], w, f=f, heads=heads, layers=2,
+                                     bf16=dtype == "bf16", sigma=sigma)
+        got = np.vstack([out[k][0][r], out[k][1][r]])
+        assert row_rel_err(got, np.vstack([R_op, R_dev])) <= tol, (r, k)
+    for a, b in zip(out[2], out[R]):
+        np.testing.assert_allclose(a, b[:2], rtol=0, atol=(2e-2 if dtype == "bf16" else 2e-6) * np.abs(a).max())
+    g.close()
