@@ -36,13 +36,13 @@ struct Tile {
     int n0;
 };
 
-template <int TM = BM>
+template <int TM = BM, int TN = BN>
 __device__ __forceinline__ Tile tile_of(const GemmArgs &G) {
     const uint32_t lb = xcd_swizzle(blockIdx.x, gridDim.x);
-    const int ct = 2 * G.F / BN;
+    const int ct = 2 * G.F / TN;
     const int64_t rt = lb / ct;
     Tile t;
-    t.n0 = (int)(lb % ct) * BN;
+    t.n0 = (int)(lb % ct) * TN;
     t.sd = rt < G.tiles0 ? 0 : 1;
     t.m0 = (rt - (t.sd ? G.tiles0 : 0)) * TM;
     return t;
@@ -352,38 +352,38 @@ __device__ __forceinline__ void column_consts(const GemmArgs &G, int sd, int n, 
 // 16x16x32 products of a 16 x 16 x 32 contraction take 3/8 of the time of
 // its eight 16x16x4 fp32 products.
 //
-// 128 x 128 block tiles, four wavefronts of 32 rows x 128 columns, so each
-// hidden row is loaded and split by one wavefront only: lanes read their H
+// 64 NI x 16 NJ block tiles (128 x 128, or 64 x 64 for few rows), four
+// wavefronts of 16 NI rows x all columns, so each hidden row is loaded and split by one wavefront only: lanes read their H
 // operands straight from global memory into registers (row l % 16 of a row
 // block, k-slice 8 (l / 16) of the 32-wide step) and split them there.  The
 // weights of the block's 128 columns pass through LDS as split planes, one
 // 32-wide k-step at a time, double-buffered, rows unpadded with XOR-swizzled
 // 16-byte chunks (as in gemm_bf16).  The next step's global loads are in
 // flight while the current step's 96 products per wavefront run.
-template <int JPH, bool ELU, bool TSP>
+template <int JPH, bool ELU, bool TSP, int NI = 2, int NJ = 8>
 __global__ void __launch_bounds__(256) gemm_f32s(GemmArgs G) {
-    constexpr int BK = 32;
-    __shared__ __attribute__((aligned(16))) uint16_t Ws[2][3][BN * BK];
-    __shared__ __attribute__((aligned(16))) float cst[4 * BN];   // column constants, 4 kinds x 128
+    constexpr int BK = 32, TN = 16 * NJ, QW = TN / 64;   // columns of the tile, weight rows per loader thread
+    __shared__ __attribute__((aligned(16))) uint16_t Ws[2][3][TN * BK];
+    __shared__ __attribute__((aligned(16))) float cst[4 * TN];   // column constants, 4 kinds
     auto sw = [](int r) { return ((r >> 1) ^ (r >> 2)) & 3; };
-    const Tile t = tile_of(G);
+    const Tile t = tile_of<64 * NI, TN>(G);
     const GemmSide S = t.sd ? G.side[1] : G.side[0];
     const float *__restrict__ H = static_cast<const float *>(S.H);
     const int F = G.F;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid < BN) {
+    if (tid < TN) {
         float v[4];
         column_consts<JPH>(G, t.sd, t.n0 + tid, v);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cst[q * BN + tid] = v[q];
+        for (int q = 0; q < 4; ++q) cst[q * TN + tid] = v[q];
     }
     // weight loader: thread -> rows tid/4 and tid/4 + 64 of the block's
     // columns, 8-wide k-chunk tid % 4 of the step
     const int lc = tid & 3;
-    const float *brow[2];
-    int loff[2];
+    const float *brow[QW];
+    int loff[QW];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+    for (int q = 0; q < QW; ++q) {
         const int lr = (tid >> 2) + 64 * q;
         const int gn = t.n0 + lr;
         brow[q] = (gn < F ? static_cast<const float *>(S.B0) + (size_t)gn * S.ldb
@@ -391,29 +391,29 @@ __global__ void __launch_bounds__(256) gemm_f32s(GemmArgs G) {
         loff[q] = lr * BK + 8 * (lc ^ sw(lr));
     }
     // hidden-row operands: row blocks i = 0, 1 of the wavefront's 32 rows
-    const int64_t rbase = t.m0 + wave * 32 + (lane & 15);
-    const float *hrow[2];
-    bool hok[2];
+    const int64_t rbase = t.m0 + wave * 16 * NI + (lane & 15);
+    const float *hrow[NI];
+    bool hok[NI];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NI; ++i) {
         hok[i] = rbase + 16 * i < S.rows;
         hrow[i] = H + (hok[i] ? rbase + 16 * i : 0) * F + 8 * (lane >> 4);
     }
-    int boff[8];
+    int boff[NJ];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         const int r = j * 16 + (lane & 15);
         boff[j] = r * BK + 8 * ((lane >> 4) ^ sw(r));
     }
-    float4 rb[2][2], rh[2][2];
+    float4 rb[QW][2], rh[NI][2];
     auto gload = [&](int k0) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        for (int q = 0; q < QW; ++q) {
             rb[q][0] = *reinterpret_cast<const float4 *>(brow[q] + k0);
             rb[q][1] = *reinterpret_cast<const float4 *>(brow[q] + k0 + 4);
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {   // rows past the end read row 0 (zeroed when split)
+        for (int i = 0; i < NI; ++i) {   // rows past the end read row 0 (zeroed when split)
             rh[i][0] = *reinterpret_cast<const float4 *>(hrow[i] + k0);
             rh[i][1] = *reinterpret_cast<const float4 *>(hrow[i] + k0 + 4);
         }
@@ -430,28 +430,28 @@ __global__ void __launch_bounds__(256) gemm_f32s(GemmArgs G) {
     };
     auto wstore = [&](int buf) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        for (int q = 0; q < QW; ++q) {
             u4 o[3];
             split8(rb[q], o);
 #pragma unroll
             for (int z = 0; z < 3; ++z) *reinterpret_cast<u4 *>(&Ws[buf][z][loff[q]]) = o[z];
         }
     };
-    bf8 ah[2][3];
+    bf8 ah[NI][3];
     auto hsplit = [&]() {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < NI; ++i) {
             u4 o[3];
             split8(rh[i], o);
 #pragma unroll
             for (int z = 0; z < 3; ++z) ah[i][z] = __builtin_bit_cast(bf8, hok[i] ? o[z] : u4{0u, 0u, 0u, 0u});
         }
     };
-    f4 acc[8][2];
+    f4 acc[NJ][NI];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) acc[j][i] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < NI; ++i) acc[j][i] = f4{0.f, 0.f, 0.f, 0.f};
     gload(0);
     wstore(0);
     hsplit();
@@ -463,7 +463,7 @@ __global__ void __launch_bounds__(256) gemm_f32s(GemmArgs G) {
         // two column blocks at a time: 24 products over four accumulators,
         // part products outer so that no two consecutive ones share one
 #pragma unroll
-        for (int jp = 0; jp < 4; ++jp) {
+        for (int jp = 0; jp < NJ / 2; ++jp) {
             bf8 bw[2][3];
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj)
@@ -476,7 +476,7 @@ __global__ void __launch_bounds__(256) gemm_f32s(GemmArgs G) {
 #pragma unroll
                 for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
+                    for (int i = 0; i < NI; ++i)
                         acc[2 * jp + jj][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                             bw[jj][PW[pp]], ah[i][PH[pp]], acc[2 * jp + jj][i], 0, 0, 0);
         }
@@ -488,10 +488,11 @@ __global__ void __launch_bounds__(256) gemm_f32s(GemmArgs G) {
     }
     // the k-step buffers are free (the loop ends with a barrier): one row
     // stage per wavefront
-    float *stage = reinterpret_cast<float *>(&Ws[0][0][0]) + wave * 32 * kStageStride;
-    static_assert(4 * 32 * kStageStride * 4 <= sizeof(Ws), "row stages must fit the k-step buffers");
-    store_rows<JPH, ELU, 2, BN, 0, 8, TSP>(G, t, rbase, t.n0, lane, acc, cst, stage);
-    store_rows<JPH, ELU, 2, BN, 4, 8, TSP>(G, t, rbase, t.n0 + 64, lane, acc, cst + 64, stage);
+    float *stage = reinterpret_cast<float *>(&Ws[0][0][0]) + wave * 16 * NI * kStageStride;
+    static_assert(4 * 16 * NI * kStageStride * 4 <= sizeof(Ws), "row stages must fit the k-step buffers");
+    store_rows<JPH, ELU, NI, TN, 0, NJ, TSP>(G, t, rbase, t.n0, lane, acc, cst, stage);
+    if constexpr (NJ == 8)
+        store_rows<JPH, ELU, NI, TN, 4, NJ, TSP>(G, t, rbase, t.n0 + 64, lane, acc, cst + 64, stage);
 }
 
 template <int JPH, int MB>
@@ -595,32 +596,47 @@ __global__ void __launch_bounds__(2 * MB) gemm_bf16(GemmArgs G) {
 
 int64_t transform_row_tiles(int64_t rows) { return (rows + BM - 1) / BM; }
 
+constexpr int64_t kSmallBlocks = 512;
 constexpr int kBf16Rows = 128;   // rows per bf16 block tile (256 measured no faster)
 
-template <int JPH>
-void launch_gemm(const GemmArgs &G, bool bf, unsigned blocks, hipStream_t st) {
+// NI x NJ: 64 NI rows x 16 NJ columns per fp32 block
+template <int JPH, int NI, int NJ>
+void launch_f32(const GemmArgs &G, unsigned blocks, hipStream_t st) {
     // the device message table: split planes at F = 256, fp32 rows below
-    if (bf) gemm_bf16<JPH, kBf16Rows><<<blocks, 2 * kBf16Rows, 0, st>>>(G);
-    else if (G.F >= 256) {
-        if (G.prep.elu) gemm_f32s<JPH, true, true><<<blocks, 256, 0, st>>>(G);
-        else gemm_f32s<JPH, false, true><<<blocks, 256, 0, st>>>(G);
+    if (G.F >= 256) {
+        if (G.prep.elu) gemm_f32s<JPH, true, true, NI, NJ><<<blocks, 256, 0, st>>>(G);
+        else gemm_f32s<JPH, false, true, NI, NJ><<<blocks, 256, 0, st>>>(G);
     } else {
-        if (G.prep.elu) gemm_f32s<JPH, true, false><<<blocks, 256, 0, st>>>(G);
-        else gemm_f32s<JPH, false, false><<<blocks, 256, 0, st>>>(G);
+        if (G.prep.elu) gemm_f32s<JPH, true, false, NI, NJ><<<blocks, 256, 0, st>>>(G);
+        else gemm_f32s<JPH, false, false, NI, NJ><<<blocks, 256, 0, st>>>(G);
     }
+}
+
+template <int JPH>
+void launch_gemm(const GemmArgs &G, bool bf, bool small, unsigned blocks, hipStream_t st) {
+    if (bf) gemm_bf16<JPH, kBf16Rows><<<blocks, 2 * kBf16Rows, 0, st>>>(G);
+    else if (small) launch_f32<JPH, 1, 4>(G, blocks, st);
+    else launch_f32<JPH, 2, 8>(G, blocks, st);
 }
 
 void launch_transform(const GemmArgs &G0, bool bf, hipStream_t st) {
     GemmArgs G = G0;
-    const int64_t bm = bf ? kBf16Rows : BM;   // rows per block tile
-    G.tiles0 = (G.side[0].rows + bm - 1) / bm;
-    const int64_t tiles1 = (G.side[1].rows + bm - 1) / bm;
-    const unsigned blocks = (unsigned)((G.tiles0 + tiles1) * (2 * G.F / BN));
+    auto tiles = [&](int s, int64_t bm) { return (G.side[s].rows + bm - 1) / bm; };
+    // fp32: 64 x 64 blocks while 128 x 128 ones leave CUs idle
+    // (fewer than two per CU): a quarter of a block's serial chain (product
+    // steps, epilogue) and of its code.  Three layers, 1,216 rows a candidate,
+    // 128 x 128 | 64 x 64, us: 1 candidate 143 | 126 (f = 128), 184 | 156 (256);
+    // 304 blocks 211 | 198, 239 | 219, 205 | 195 (f = 64); 513 blocks 245 | 235
+    // (64); 608 blocks 265 | 264, 299 | 300; 760 blocks 285 | 293 (128).
+    const bool small = !bf && (tiles(0, BM) + tiles(1, BM)) * (2 * G.F / BN) < kSmallBlocks;
+    const int64_t bm = bf ? kBf16Rows : small ? 64 : BM;   // rows per block tile
+    G.tiles0 = tiles(0, bm);
+    const unsigned blocks = (unsigned)((G.tiles0 + tiles(1, bm)) * (2 * G.F / (small ? 64 : BN)));
     switch (G.prep.jph) {
-        case 1: launch_gemm<1>(G, bf, blocks, st); break;
-        case 2: launch_gemm<2>(G, bf, blocks, st); break;
-        case 4: launch_gemm<4>(G, bf, blocks, st); break;
-        default: launch_gemm<0>(G, bf, blocks, st); break;
+        case 1: launch_gemm<1>(G, bf, small, blocks, st); break;
+        case 2: launch_gemm<2>(G, bf, small, blocks, st); break;
+        case 4: launch_gemm<4>(G, bf, small, blocks, st); break;
+        default: launch_gemm<0>(G, bf, small, blocks, st); break;
     }
 }
 

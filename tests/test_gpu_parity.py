@@ -494,3 +494,27 @@ def test_op_tile_parts_and_whole_tiles(f, heads, dtype, sigma):
     for a, b in zip(out[2], out[R]):
         np.testing.assert_allclose(a, b[:2], rtol=0, atol=(2e-2 if dtype == "bf16" else 2e-6) * np.abs(a).max())
     g.close()
+
+
+@pytest.mark.parametrize("f,heads,sigma,R", [(64, 4, "relu", 1010), (64, 1, "elu", 1010), (128, 8, "relu", 505),
+                                             (128, 2, "elu", 505), (256, 16, "relu", 253), (256, 1, "elu", 253),
+                                             (64, 4, "relu", 985), (128, 4, "relu", 3), (256, 4, "elu", 1)])
+def test_fp32_transform_block_shapes(f, heads, sigma, R):
+    """65 ops and 2 devices: 128 x 128 blocks of the fp32 relation transform from 512 of them on, 64 x 64 below
+    (985 replicas at f = 64: the last count below; 1 and 3: a ragged first block)."""
+    n, m = 65, 2
+    rng = np.random.default_rng((2302, 93, f, heads, R))
+    topo = mk_topo(n, m, oo=[(i, i + 1) for i in range(n - 1)], dd=[(0, 1)])
+    w = synth.make_weights(f, heads, 2, 42, f, bias_scale=0.2, seed_extra=f + heads)
+    x = [rng.uniform(-1, 1, (R, n, 42)).astype(np.float32), rng.uniform(-1, 1, (R, m, 8)).astype(np.float32),
+         rng.uniform(-1, 1, topo.e_oo).astype(np.float32), rng.uniform(-1, 1, (R, topo.e_dd, 2)).astype(np.float32),
+         rng.integers(0, 2, (R, topo.e_od)).astype(np.uint8)]
+    g = P.Graph([topo])
+    mod = P.Model(w, f=f, heads=heads, layers=2, f_op=42, sigma=sigma)
+    E_op, E_dev = P.forward(g, mod, *(dev_tensor(a) for a in x))
+    for r in {0, R // 2, R - 1}:
+        R_op, R_dev = oracle.forward(topo, x[0][r], x[1][r], x[2], x[3][r], x[4][r], w, f=f, heads=heads, layers=2,
+                                     sigma=sigma)
+        got = np.vstack([E_op[r].cpu().numpy(), E_dev[r].cpu().numpy()])
+        assert row_rel_err(got, np.vstack([R_op, R_dev])) <= 1e-5, r
+    g.close()
