@@ -29,8 +29,10 @@ __global__ void __launch_bounds__(256) small_gemm(SmallGemm G, int vec) {
 // columns in LDS as exact bf16 split planes (staged once per block, so blocks
 // are persistent), the unit's raw features read straight into operand
 // registers (lane l: row l % 16, features 8 (l / 16) .. + 7 of a 32-wide step)
-// with the next unit's in flight, six part products per step on bf16 MFMAs (the fp32 contraction up to fp32 rounding,
-// at 3/8 of the matrix-core time of 16x16x4 products).  Products are taken as
+// with the next unit's in flight, eight part products per step on bf16 MFMAs
+// (the fp32 contraction up to fp32 rounding, at half of the matrix-core time of
+// 16x16x4 products; the two more than the transform's six cost nothing
+// measurable beside the writes).  Products are taken as
 // C^T, so a lane owns four columns of its row; rows leave through the
 // wavefront's LDS stage as whole 256-byte segments.  Bound by the HBM write of
 // C.  K = 42: 768,000 rows x 256 fp32 columns 330 -> 221 us (4.1 TB/s),
@@ -110,23 +112,29 @@ __global__ void __launch_bounds__(512, 4) enc_rows(SmallGemm G, int halves) {
             for (int z = 0; z < 3; ++z) a[s][z] = as_bf8(p[0][z], p[1][z], p[2][z], p[3][z]);
         }
         if (unit + step < units) load(unit + step);
-        constexpr int PW[6] = {2, 1, 0, 1, 0, 0}, PX[6] = {0, 1, 2, 0, 1, 0};   // smallest first
+        // Smallest first, the large products of every step last.  With six products,
+        // step by step, more pre-activations near zero fell on the wrong side of the
+        // ReLU: encoder gradients of 64 candidates of 1,200 ops, 16 seeds, were 9.3e-6
+        // from float64 (geometric mean) against 7.1e-6 on fp32 products, 7.7e-6 so.
+        constexpr int NP = 8, PW[NP] = {2, 1, 2, 1, 0, 1, 0, 0}, PX[NP] = {1, 2, 0, 1, 2, 0, 1, 0};
 #pragma unroll
         for (int hh = 0; hh < NJ / 4; ++hh) {
             f4 acc[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 acc[j] = f4{0.f, 0.f, 0.f, 0.f};
+                bf8 b[NS][3];
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
                     const int o = woff[s] < 0 ? NJ * 16 * KS : woff[s] + (4 * hh + j) * 16 * KS;
-                    bf8 b[3];
 #pragma unroll
-                    for (int z = 0; z < 3; ++z) b[z] = *reinterpret_cast<const bf8 *>(&W[z][o]);
-#pragma unroll
-                    for (int p = 0; p < 6; ++p)
-                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[PW[p]], a[s][PX[p]], acc[j], 0, 0, 0);
+                    for (int z = 0; z < 3; ++z) b[s][z] = *reinterpret_cast<const bf8 *>(&W[z][o]);
                 }
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+#pragma unroll
+                    for (int s = 0; s < NS; ++s)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[s][PW[p]], a[s][PX[p]], acc[j], 0, 0, 0);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
