@@ -41,7 +41,7 @@ TRANSFORM_PEAK = {"f32": PEAK_F32_SPLIT_TFLOPS, "bf16": PEAK_TFLOPS["bf16"]}
 # fp32 vector (VALU) peak without packed-fp32 instructions, which this build
 # does not generate: 256 CUs x 4 SIMDs x 16 lanes x 2 flops (FMA) x 2.4 GHz
 PEAK_VALU_F32_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
-KERNEL_NAMES = {"graph_build": "graph build kernels", "encode": "small_gemm (encoders)",
+KERNEL_NAMES = {"graph_build": "graph build kernels", "encode": "enc_rows, fwd_prologue (node encoders, pass set-up)",
                 "transform": "gemm_f32s / gemm_bf16", "agg_op_op": "agg_op (per-row path)", "agg_op_dev": "agg_op_tile",
                 "agg_dev_op": "agg_b2", "agg_dev_merge": "agg_dev_final", "dev_prep": "prep_rows",
                 "decide": "decide kernels"}

@@ -23,7 +23,7 @@ extern "C" {
  * where noted). */
 enum {
     TAG_STAGE_GRAPH_BUILD = 0,    /* all kernels of tag_graph_build (one pair per call)      */
-    TAG_STAGE_ENCODE = 1,         /* node encoders (op and device launches, one pair)        */
+    TAG_STAGE_ENCODE = 1,         /* node encoders and what a pass prepares from its inputs  */
     TAG_STAGE_TRANSFORM = 2,      /* relation transforms W^h h, op and device rows (1/layer) */
     TAG_STAGE_AGG_OP_OP = 3,      /* op <- op aggregation (1/layer); on the path for heads   */
                                   /* narrower than 16 channels this also covers op <- dev    */

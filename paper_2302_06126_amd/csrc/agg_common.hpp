@@ -109,10 +109,6 @@ struct AggArgs {
     float *xcsr; int64_t s_xcsr;      // [xrep][nnz of B0], xrep = 1 (shared features) or R
 };
 
-// MFMA path (agg_mfma.hip): whether the tile path takes a layer: heads of 16 to F channels (K <= 16),
-// and the per-candidate transform rows (n_op 2F elements of esz bytes) and
-// the device message table (three parts of R n_dev F words) addressed by
-// 32-bit byte offsets
 // Parts an op tile is cut into for the op destinations (1 or kTileParts).  With
 // few tiles a block's serial chain (prologue loads, four rows per lane group)
 // is the time, not the chip's rate; with more of them the parts repeat the
@@ -122,6 +118,11 @@ struct AggArgs {
 // 400, 251 | 253, bf16 331 | 343; 760 tiles 294 | 303 (128), bf16 385 | 428.
 constexpr int kTileParts = 4;
 inline int op_tile_parts(int64_t n_tiles, int64_t R, bool bf) { return n_tiles * R < (bf ? 256 : 384) ? kTileParts : 1; }
+
+// MFMA path (agg_mfma.hip): whether the tile path takes a layer: heads of 16 to F channels (K <= 16),
+// and the per-candidate transform rows (n_op 2F elements of esz bytes) and
+// the device message table (three parts of R n_dev F words) addressed by
+// 32-bit byte offsets
 bool mfma_path_supported(int F, int K, int64_t n_op, int64_t R, int64_t n_dev, int esz);
 bool launch_agg_mfma(int F, int K, bool bf, const AggArgs &A, hipStream_t st);
 

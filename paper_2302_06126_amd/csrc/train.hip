@@ -829,10 +829,8 @@ __global__ void bwd_combine(BwdLayer P, BwdSrc S, int K) {
 // ------------------------------------------------------- op-device tiles
 // Op-device links carry only the placement bit, so a device row's message
 // has two forms (bit 0 / 1).  One block per (replica, tile of consecutive
-// ops of one topology) stages the topology's device message rows, gradient
-// rows and attention terms in LDS and walks the tile's ops: op rows are
-// read once, and both directions of every op-device link are handled from
-// the op's side (the long device rows are never walked).
+// ops of one topology) handles both directions of the tile's op-device links
+// from the op's side (the long device rows are never walked).
 struct OdTile {
     const int32_t *tiles;          // [n_tiles][3]: first op (global), op count, topology
     const int32_t *dev_off;        // [G+1]
