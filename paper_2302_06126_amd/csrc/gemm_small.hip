@@ -26,75 +26,59 @@ __global__ void __launch_bounds__(256) small_gemm(SmallGemm G, int vec) {
 
 // Node encoders of many rows (K <= 64, columns a multiple of 64): wavefronts
 // that run over 16-row units on their own, the weights of the block's NJ * 16
-// columns in LDS as exact bf16 split planes (staged once per block, so blocks
-// are persistent), the unit's raw features read straight into operand
-// registers (lane l: row l % 16, features 8 (l / 16) .. + 7 of a 32-wide step)
-// with the next unit's in flight, eight part products per step on bf16 MFMAs
-// (the fp32 contraction up to fp32 rounding, at half of the matrix-core time of
-// 16x16x4 products; the two more than the transform's six cost nothing
-// measurable beside the writes).  Products are taken as
-// C^T, so a lane owns four columns of its row; rows leave through the
-// wavefront's LDS stage as whole 256-byte segments.  Bound by the HBM write of
-// C.  K = 42: 768,000 rows x 256 fp32 columns 330 -> 221 us (4.1 TB/s),
-// 2,560,000 x 256 bf16 860 -> 508 us, 6,144,000 x 128 fp32 1.25 -> 0.92 ms (4.5
-// TB/s) against 64-row blocks on 16x16x4 products.
+// columns in LDS (staged once per block, so blocks are persistent), the unit's
+// raw features read straight into operand registers with the next unit's in
+// flight.  fp32 16x16x4 products in the order of the 16-row blocks (k ascending,
+// then the bias), so a row's values do not depend on how many rows a call has.
+// Products are taken as C^T, so a lane owns four columns of its row; rows leave
+// through the wavefront's LDS stage as whole 256-byte segments.
+// Bound by the HBM write of C where C outgrows the last-level cache, with the matrix
+// cores busy for about two thirds of it: against 64-row blocks, K = 42: 2,560,000
+// rows x 256 bf16 columns 848 -> 598 us, fp32 1.03 -> 0.86 ms (3.1 TB/s), 1,500,000 x
+// 128 fp32 299 -> 249 us.  (On exact bf16 splits the last was 237 us and the first
+// 548, but sums in another order round other hidden values to the next bf16, and an
+// infinite feature became a NaN and by the ReLU a zero.)
 template <int NJ, int KP, bool BF>
 __global__ void __launch_bounds__(512, 4) enc_rows(SmallGemm G, int halves) {
-    constexpr int NS = (KP + 31) / 32;   // 32-wide steps; KP = 32, 48 or 64 features have room in LDS
-    // plane row stride (bf16 elements): rows 16-byte aligned, eight rows on distinct banks
-    constexpr int KS = KP == 48 ? 48 : KP + 8;
+    constexpr int NS = KP / 4;   // products per 16 x 16 tile; KP = 16, 32, 48 or 64 features
+    // LDS weight row of a column: for each lane group lg its operands k = lg, 4 + lg, 8 + lg, ...
+    // one after the other (read four at a time); the stride keeps eight rows on distinct banks
+    constexpr int WS = KP + 4;
     constexpr int SP = 64 + 4;   // stage row stride (floats)
-    __shared__ __attribute__((aligned(16))) uint16_t W[3][NJ * 16 * KS + 8];   // + eight zeros
-    __shared__ __attribute__((aligned(16))) float bias[NJ * 16], stage[8][16 * SP];
+    __shared__ __attribute__((aligned(16))) float W[NJ * 16 * WS], bias[NJ * 16], stage[8][16 * SP];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lg = lane >> 4;
     // the column halves of a row share an XCD (and its L2)
     const uint32_t lb = xcd_swizzle(blockIdx.x, gridDim.x);
     const int n0 = (int)(lb % halves) * NJ * 16, K = G.K;
     {
-        constexpr int NP = NJ * 16 * KP / 2 / 512;   // weight pairs per thread, their loads issued together
-        float w[NP][2];
+        constexpr int NP = NJ * 16 * KP / 512;   // weights per thread, their loads issued together
+        float w[NP];
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
-            const int i = threadIdx.x + 512 * q, k = 2 * (i % (KP / 2));
-            const float *b = G.B + (int64_t)(n0 + i / (KP / 2)) * G.ldb;
-            w[q][0] = k < K ? b[k] : 0.f;
-            w[q][1] = k + 1 < K ? b[k + 1] : 0.f;
+            const int i = threadIdx.x + 512 * q, k = i % KP;
+            w[q] = k < K ? G.B[(int64_t)(n0 + i / KP) * G.ldb + k] : 0.f;
         }
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
-            const int i = threadIdx.x + 512 * q, o = i / (KP / 2) * KS + 2 * (i % (KP / 2));
-            unsigned p[3];
-            split3(w[q][0], w[q][1], p);
-#pragma unroll
-            for (int z = 0; z < 3; ++z) *reinterpret_cast<unsigned *>(&W[z][o]) = p[z];
+            const int i = threadIdx.x + 512 * q, k = i % KP;
+            W[i / KP * WS + (k & 3) * NS + (k >> 2)] = w[q];
         }
     }
-    if (threadIdx.x < 24) W[threadIdx.x / 8][NJ * 16 * KS + threadIdx.x % 8] = 0;
     for (int i = threadIdx.x; i < NJ * 16; i += 512) bias[i] = G.bias ? G.bias[n0 + i] : 0.f;
     __syncthreads();
     const int64_t units = (G.rows + 15) / 16, step = (int64_t)(gridDim.x / halves) * 8;
-    float x[NS][8];
-    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // rows of K floats: 4-byte aligned
+    // lane l's operands: row l % 16 of the unit, features l / 16, 4 + l / 16, ... (zero from K on)
+    float x[NS];
     auto load = [&](int64_t unit) {
         const int64_t r = unit * 16 + lr;
         const float *p = G.A + (r < G.rows ? r : G.rows - 1) * G.lda;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const int k = 32 * s + 8 * lg;
-            if (K >= 32 * (s + 1)) {
-                const f4u a = *reinterpret_cast<const f4u *>(p + k), b = *reinterpret_cast<const f4u *>(p + k + 4);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { x[s][i] = a[i]; x[s][4 + i] = b[i]; }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) x[s][i] = k + i < K ? p[k + i] : 0.f;
-            }
+            const int k = 4 * s + lg;
+            x[s] = k < K ? p[k] : 0.f;
         }
     };
-    // the lane's slice of a weight row in each step (past KP: the zeros)
-    int woff[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) woff[s] = 32 * s + 8 * lg < KP ? lr * KS + 32 * s + 8 * lg : -1;
+    const float *wl = W + lr * WS + lg * NS;
     int64_t unit = (int64_t)(lb / halves) * 8 + wave;
     if (unit < units) load(unit);
     float *st = stage[wave];
@@ -102,39 +86,25 @@ __global__ void __launch_bounds__(512, 4) enc_rows(SmallGemm G, int halves) {
         // (the weights are read afresh for every unit: held in registers across
         // the loop they would not fit)
         asm volatile("" ::: "memory");
-        bf8 a[NS][3];
+        float a[NS];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            unsigned p[4][3];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) split3(x[s][2 * i], x[s][2 * i + 1], p[i]);
-#pragma unroll
-            for (int z = 0; z < 3; ++z) a[s][z] = as_bf8(p[0][z], p[1][z], p[2][z], p[3][z]);
-        }
+        for (int s = 0; s < NS; ++s) a[s] = x[s];
         if (unit + step < units) load(unit + step);
-        // Smallest first, the large products of every step last.  With six products,
-        // step by step, more pre-activations near zero fell on the wrong side of the
-        // ReLU: encoder gradients of 64 candidates of 1,200 ops, 16 seeds, were 9.3e-6
-        // from float64 (geometric mean) against 7.1e-6 on fp32 products, 7.7e-6 so.
-        constexpr int NP = 8, PW[NP] = {2, 1, 2, 1, 0, 1, 0, 0}, PX[NP] = {1, 2, 0, 1, 2, 0, 1, 0};
 #pragma unroll
         for (int hh = 0; hh < NJ / 4; ++hh) {
             f4 acc[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                acc[j] = f4{0.f, 0.f, 0.f, 0.f};
-                bf8 b[NS][3];
+            for (int j = 0; j < 4; ++j) acc[j] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    const int o = woff[s] < 0 ? NJ * 16 * KS : woff[s] + (4 * hh + j) * 16 * KS;
+            for (int s4 = 0; s4 < NS; s4 += 4) {
+                f4 b[4];
 #pragma unroll
-                    for (int z = 0; z < 3; ++z) b[s][z] = *reinterpret_cast<const bf8 *>(&W[z][o]);
-                }
+                for (int j = 0; j < 4; ++j) b[j] = *reinterpret_cast<const f4 *>(wl + (4 * hh + j) * 16 * WS + s4);
 #pragma unroll
-                for (int p = 0; p < NP; ++p)
+                for (int s = 0; s < 4; ++s)
 #pragma unroll
-                    for (int s = 0; s < NS; ++s)
-                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[s][PW[p]], a[s][PX[p]], acc[j], 0, 0, 0);
+                    for (int j = 0; j < 4; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][s], a[s4 + s], acc[j], 0, 0, 0);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -180,15 +150,21 @@ void launch_enc(const SmallGemm &G, hipStream_t st) {
 
 template <int NJ>
 void launch_enc_k(const SmallGemm &G, hipStream_t st) {
-    if (G.K <= 32) launch_enc<NJ, 32>(G, st);
+    if (G.K <= 16) launch_enc<NJ, 16>(G, st);
+    else if (G.K <= 32) launch_enc<NJ, 32>(G, st);
     else if (G.K <= 48) launch_enc<NJ, 48>(G, st);
     else launch_enc<NJ, 64>(G, st);
 }
 
-// rows from which an encoder takes enc_rows: at least one unit for each
-// wavefront of an eighth of the chip; below, staging the weights costs more than
-// the rows (1,024 rows: 4.7 us in 16-row blocks of small_gemm)
-constexpr int64_t kEncRows = 8192;
+// Rows from which an encoder takes enc_rows.  64 columns: where the 16-row
+// blocks end (20,000 to 1,500,000 rows of 8 to 64 features, 64-row tiles | here:
+// 42 features 14.9 | 10.7 us at 60,000, 37.6 | 25.1 at 200,000, 247 | 152 at
+// 1,500,000; no case slower).  More columns: where the writes of C no longer stay
+// in the last-level cache (42 features, 128 columns 31 | 34 us at 140,000,
+// 74 | 77 at 400,000, 114 | 103 at 550,000; 256 columns 94 | 101 at 270,000,
+// 227 | 193 at 550,000; bf16 27 | 31 for 140,000 x 128, 171 | 141 for 550,000 x
+// 256); with fewer, wavefronts of two or three units leave the chip uneven.
+inline int64_t enc_rows_from(int N) { return N <= 64 ? 16384 : int64_t(1) << 19; }
 
 template <int SM, int SK, int WM>
 void launch_tile(const SmallGemm &G, int vec, hipStream_t st) {
@@ -202,14 +178,17 @@ namespace {
 enum class Route { kFew, kTiles, kEncoder, kSplit };
 
 Route route_of(const SmallGemm &G) {
+    // encoders (the contractions with a ReLU) keep fp32 products in one order
+    // whatever their size; their kernel takes whole 64-column blocks of aligned rows
+    if (G.relu && G.K <= 64 && G.rows >= enc_rows_from(G.N) && vec_ok(G) && !G.row_map && G.N % 64 == 0)
+        return Route::kEncoder;
     // wide contractions of many rows (the decoder's projections for a whole
     // group of every candidate): split products (42,496 + 16,384 rows: 70
     // against 112 us).  Fewer rows than 128 blocks of 64 leave the chip idle
     // either way and keep the 16-row blocks.
-    if (G.K >= 64 && G.rows >= 8192 && !G.c_bf16) return Route::kSplit;
-    if (G.K <= 64 && G.rows >= kEncRows && vec_ok(G) && !G.row_map && G.N % 64 == 0) return Route::kEncoder;
-    // fewer than 256 blocks of 64 rows (the decoder projections, the device
-    // encoder): 16-row blocks and 32-wide k-chunks, so that more compute units
+    if (!G.relu && !G.bias && G.K >= 64 && G.rows >= 8192 && !G.c_bf16) return Route::kSplit;
+    // fewer than 256 blocks of 64 rows (the decoder projections, the encoders of
+    // small calls): 16-row blocks and 32-wide k-chunks, so that more compute units
     // work and fewer dependent load rounds separate the chunks
     return (G.rows + 63) / 64 < 256 ? Route::kFew : Route::kTiles;
 }
@@ -226,7 +205,6 @@ void launch_small_gemm(const SmallGemm &G, hipStream_t st) {
             S.B = G.B; S.ldb = G.ldb;
             S.M = G.rows; S.N = G.N; S.K = S.k_per = G.K;
             S.ones_col = -1;
-            S.bias = G.bias; S.relu = G.relu;
             S.C = static_cast<float *>(G.C); S.ldc = G.ldc;
             launch_split_gemm(S, true, true, 1, st);
             break;

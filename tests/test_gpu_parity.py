@@ -443,11 +443,12 @@ def test_decide_query_groups(m_dev, f, H, S, scale):
 
 @pytest.mark.parametrize("f_op,f,dtype", [(1, 64, "f32"), (31, 128, "bf16"), (32, 256, "f32"), (33, 64, "bf16"),
                                           (42, 128, "f32"), (47, 256, "bf16"), (48, 64, "f32"), (49, 128, "f32"),
-                                          (64, 256, "bf16"), (63, 64, "f32")])
+                                          (64, 256, "bf16"), (63, 64, "f32"),
+                                          (16, 128, "f32"), (17, 64, "f32"), (64, 64, "f32"), (64, 256, "f32")])
 def test_encoder_feature_widths_many_rows(f_op, f, dtype):
-    """8,241 op rows (a last unit of one row): feature widths at and around the 32-wide steps and the 48-feature
-    weight rows, odd widths (rows 4-byte aligned), 64 to 256 columns."""
-    n, R = 41, 201
+    """16,441 op rows at 64 columns and 524,747 above (where the encoder kernel takes over; a ragged last unit):
+    feature widths at and around the 16-, 32- and 48-feature weight rows, odd widths (rows 4-byte aligned)."""
+    n, R = (41, 401) if f == 64 else (409, 1283)
     topo = synth.random_topology(900 + f_op, n, 3, 60)
     rng = np.random.default_rng((2302, 91, f_op))
     w = synth.make_weights(f, 4, 1, f_op, f, bias_scale=0.3, seed_extra=f_op)
@@ -472,7 +473,7 @@ def test_encoder_feature_widths_many_rows(f_op, f, dtype):
 def test_op_tile_parts_and_whole_tiles(f, heads, dtype, sigma):
     """65 ops (a tile of 64, one of one op): two replicas take 16-row parts of the tiles, 200 take whole tiles; a
     hub op with more links than a part stages at a time.  Both against the oracle, and the replicas they share
-    against each other to the encoders' rounding."""
+    against each other."""
     n, m, R = 65, 5, 200
     rng = np.random.default_rng((2302, 92, f, heads))
     topo = mk_topo(n, m, oo=[(i, i + 1) for i in range(n - 1)] + [(3, j) for j in range(5, n)] +
@@ -517,4 +518,55 @@ def test_fp32_transform_block_shapes(f, heads, sigma, R):
                                      sigma=sigma)
         got = np.vstack([E_op[r].cpu().numpy(), E_dev[r].cpu().numpy()])
         assert row_rel_err(got, np.vstack([R_op, R_dev])) <= 1e-5, r
+    g.close()
+
+
+def _encoder_case(f_op, f, dtype, n, R):
+    topo = synth.random_topology(900 + f_op, n, 3, 60)
+    rng = np.random.default_rng((2302, 94, f_op, R))
+    w = synth.make_weights(f, 4, 1, f_op, f, bias_scale=0.3, seed_extra=f_op)
+    x = [rng.uniform(-1, 1, (R, n, f_op)).astype(np.float32), rng.uniform(-1, 1, (R, 3, 8)).astype(np.float32),
+         rng.uniform(-1, 1, topo.e_oo).astype(np.float32), rng.uniform(-1, 1, (R, topo.e_dd, 2)).astype(np.float32),
+         rng.integers(0, 2, (R, topo.e_od)).astype(np.uint8)]
+    g = P.Graph([topo])
+    m = P.Model(w, f=f, heads=4, layers=1, f_op=f_op, dtype=dtype)
+    return g, m, x
+
+
+def _forward_of(g, m, x, rs):
+    part = [a if i == 2 else np.ascontiguousarray(a[rs]) for i, a in enumerate(x)]
+    return [e.cpu().numpy() for e in P.forward(g, m, *(dev_tensor(a) for a in part))]
+
+
+@pytest.mark.parametrize("f_op,f,dtype,n,R", [(42, 64, "f32", 41, 201), (42, 256, "bf16", 41, 201),
+                                              (42, 64, "f32", 41, 401), (42, 128, "bf16", 41, 401),
+                                              (64, 256, "f32", 41, 401), (64, 64, "f32", 41, 1700),
+                                              (33, 64, "bf16", 41, 1700), (42, 128, "f32", 409, 1283),
+                                              (7, 128, "bf16", 409, 1283), (50, 256, "f32", 409, 1283),
+                                              (42, 256, "bf16", 409, 1283)])
+def test_encoder_rows_do_not_depend_on_the_batch(f_op, f, dtype, n, R):
+    """8,241 op rows (16-row blocks), 16,441 (64-row tiles, at 64 columns the encoder kernel with one unit per
+    wavefront) and 69,700 or 524,747 (several units): every kernel adds the products in one order, so a candidate's
+    embeddings are the same bits alone and in the batch."""
+    g, m, x = _encoder_case(f_op, f, dtype, n, R)
+    many = _forward_of(g, m, x, slice(None))
+    for rs in (slice(0, 3), slice(R // 2, R // 2 + 2), slice(R - 2, R)):
+        for a, b in zip(many, _forward_of(g, m, x, rs)):
+            np.testing.assert_array_equal(a[rs], b)
+    g.close()
+
+
+@pytest.mark.parametrize("f_op,f,dtype", [(42, 64, "f32"), (42, 64, "bf16"), (42, 256, "bf16"), (64, 128, "f32")])
+def test_encoder_non_finite_features_many_rows(f_op, f, dtype):
+    """An infinite feature gives what it gives in a call of few rows: an infinity where its weight is positive, so
+    rows that show it, and not a row of zeros."""
+    g, m, x = _encoder_case(f_op, f, dtype, 41, 401)
+    x[0][5, 7, 3], x[0][100, 40, f_op - 1], x[0][400, 0, 0] = np.inf, -np.inf, np.nan
+    many = _forward_of(g, m, x, slice(None))
+    for r in (5, 100, 400, 6):
+        few = _forward_of(g, m, x, slice(r, r + 1))
+        for a, b in zip(many, few):
+            np.testing.assert_array_equal(a[r:r + 1], b)
+    assert not np.isfinite(many[0][5]).all() and not np.isfinite(many[0][100]).all()
+    assert np.isfinite(many[0][6]).all()
     g.close()
