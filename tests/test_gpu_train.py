@@ -232,3 +232,34 @@ def test_train_argument_checks(torch):
     with pytest.raises(_abi.TagError) as e:
         tr.step(feats)
     assert e.value.status == _abi.TAG_ENOSPACE
+
+
+def test_long_weight_gradient_has_no_bias(torch):
+    """The decoder's device weights, summed over 81,000 device rows of gradients of either sign.  Hidden units h and
+    h + 64 have the same weights and opposite readouts, so the gradients of their rows are opposite bit for bit, and so
+    are their exact sums: what is left of the two sums is rounding.  Roundings of either sign (1e-7 of the rms each)
+    average to 2e-9 over 64 x 64 outputs; sums rounded towards minus infinity leave their bias, 1.4e-7 here."""
+    import paper_2302_06126_amd.train as PT
+    f, H, S, R, n, m = 64, 128, 32, 27000, 2, 3
+    topo = synth.random_topology(77, n, m, 1)
+    rng = np.random.default_rng((2302, 95))
+    w = synth.make_weights(f, 4, 1, 42, H, bias_scale=0.3)
+    for k, sign in (("dec_w1", 1), ("dec_b1", 1), ("dec_w2", -1)):
+        w[k][H // 2:] = sign * w[k][:H // 2]
+    masks = rng.integers(1, 1 << m, S).astype(np.uint64)
+    opts = rng.integers(0, 4, S).astype(np.uint8)
+    target = rng.random((R, S)) ** 8
+    x = [rng.uniform(-1, 1, (R, n, 42)).astype(np.float32), rng.uniform(-1, 1, (R, m, 8)).astype(np.float32),
+         rng.uniform(-1, 1, topo.e_oo).astype(np.float32), rng.uniform(-1, 1, (R, topo.e_dd, 2)).astype(np.float32),
+         rng.integers(0, 2, (R, topo.e_od)).astype(np.uint8)]
+    g = P.Graph([topo])
+    mod = P.Model(w, f=f, heads=4, layers=1, f_op=42, dec_hidden=H)
+    dev = [torch.from_numpy(a).cuda() for a in x]
+    tr = PT.Trainer(g, mod, R, masks, opts, np.arange(R), np.zeros(R), rng.integers(0, n, R))
+    tr.set_targets(target / target.sum(axis=1, keepdims=True))
+    tr.step(P.make_features(*dev))
+    got = tr.grads["dec_w1"].cpu().numpy().reshape(H, 2 * f + 4)[:, :f].astype(np.float64)
+    left = (got[:H // 2] + got[H // 2:]) / 2 / np.sqrt((got ** 2).mean())
+    _say(f"[train] long weight gradient: mean left {left.mean():.1e}, rms {np.sqrt((left ** 2).mean()):.1e}")
+    assert np.sqrt((left ** 2).mean()) <= 1e-6 and abs(left.mean()) <= 2e-8
+    g.close()
