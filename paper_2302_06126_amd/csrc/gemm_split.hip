@@ -1,5 +1,5 @@
-// General fp32 GEMM on the bf16 matrix cores: C[m][n] (+)= act(bias[n] +
-// sum_k a(m, k) b(n, k)), both operands split exactly into three bf16 parts as
+// General fp32 GEMM on the bf16 matrix cores: C[m][n] = sum_k a(m, k) b(n, k),
+// both operands split exactly into three bf16 parts as
 // they are staged, six part products per 16x16x32 step (the fp32 contraction
 // up to fp32 rounding, as in the relation transform, at 3/8 of the matrix-core
 // time of fp32 16x16x4 products).  Used where K is at least one 32-wide step:
@@ -178,31 +178,17 @@ __global__ void __launch_bounds__(256) gemm_s3(SplitGemm G) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int64_t n = n0 + wn * (TN / WN) + j * 16 + 4 * (lane >> 4);
-        float bias[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) bias[v] = G.bias && n + v < G.N ? G.bias[n + v] : 0.f;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int64_t m = m0 + wm * (TM / WM) + i * 16 + (lane & 15);
             if (m >= G.M || n >= G.N) continue;
             float *p = C + m * G.ldc + n;
-            float x[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                x[v] = acc[j][i][v] + bias[v];
-                if (G.relu) x[v] = fmaxf(x[v], 0.f);
-            }
             if (G.cvec && n + 4 <= G.N) {
-                float4 o = make_float4(x[0], x[1], x[2], x[3]);
-                if (G.accumulate) {
-                    const float4 c = *reinterpret_cast<const float4 *>(p);
-                    o.x += c.x; o.y += c.y; o.z += c.z; o.w += c.w;
-                }
-                *reinterpret_cast<float4 *>(p) = o;
+                *reinterpret_cast<f4 *>(p) = acc[j][i];
             } else {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (n + v < G.N) p[v] = G.accumulate ? p[v] + x[v] : x[v];
+                    if (n + v < G.N) p[v] = acc[j][i][v];
             }
         }
     }
@@ -211,10 +197,9 @@ __global__ void __launch_bounds__(256) gemm_s3(SplitGemm G) {
 template <int TM, int TN>
 void launch_tile(const SplitGemm &G, bool a_kc, bool b_kc, int64_t splits, hipStream_t st) {
     const dim3 grid((unsigned)((G.M + TM - 1) / TM), (unsigned)((G.N + TN - 1) / TN), (unsigned)splits);
-    if (a_kc && b_kc) gemm_s3<TM, TN, true, true><<<grid, 256, 0, st>>>(G);
-    else if (a_kc) gemm_s3<TM, TN, true, false><<<grid, 256, 0, st>>>(G);
-    else if (b_kc) gemm_s3<TM, TN, false, true><<<grid, 256, 0, st>>>(G);
-    else gemm_s3<TM, TN, false, false><<<grid, 256, 0, st>>>(G);
+    if (!a_kc) gemm_s3<TM, TN, false, false><<<grid, 256, 0, st>>>(G);
+    else if (b_kc) gemm_s3<TM, TN, true, true><<<grid, 256, 0, st>>>(G);
+    else gemm_s3<TM, TN, true, false><<<grid, 256, 0, st>>>(G);
 }
 
 bool al16(const void *p, int64_t ld) { return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 4 == 0; }

@@ -111,9 +111,9 @@ struct SmallGemm {
 void launch_small_gemm(const SmallGemm &G, hipStream_t st);
 bool small_gemm_few(const SmallGemm &G);   // takes the 16-row blocks of few rows
 
-// C[m][n] (+)= act(bias[n] + sum_k a(m, k) b(n, k)) over exact bf16 splits of
-// fp32 operands (gemm_split.hip): a(m, k) = A[row(m)][k] (a_kc) or A[k][m],
-// b(n, k) = B[n][k] (b_kc) or B[k][n], column ones_col of B reading as ones;
+// C[m][n] = sum_k a(m, k) b(n, k) over exact bf16 splits of fp32 operands
+// (gemm_split.hip): a(m, k) = A[row(m)][k] (a_kc) or A[k][m], b(n, k) =
+// B[n][k] (b_kc, with a_kc only) or B[k][n], column ones_col of B reading as ones;
 // split s of the k range [s k_per, (s + 1) k_per) goes to C + s c_split.
 struct SplitGemm {
     const float *A;
@@ -123,12 +123,9 @@ struct SplitGemm {
     int64_t ldb;
     int64_t M, N, K;
     int64_t ones_col;         // -1: none
-    const float *bias;        // optional
-    int relu;
     float *C;
     int64_t ldc, c_split;
     int64_t k_per;            // a multiple of 32 when there are several splits
-    int accumulate;
     int vec, cvec;            // set by the launcher: 16-byte accesses allowed
 };
 void launch_split_gemm(SplitGemm G, bool a_kc, bool b_kc, int64_t splits, hipStream_t st);
