@@ -4,7 +4,8 @@
 // up to fp32 rounding, as in the relation transform, at 3/8 of the matrix-core
 // time of fp32 16x16x4 products).  Used where K is at least one 32-wide step:
 // the decoder's projections of many rows and the training step's gradients of
-// the hidden rows and of the weights (split over K).
+// the hidden rows and of the weights (split over K).  Operands and results that
+// are not finite give what fp32 products give.
 //
 // Bound by the staging (loads, splits, LDS) more than by the products: a block
 // of TM x TN outputs keeps one k-step of split planes in LDS (48 KiB at 128 x
@@ -135,7 +136,8 @@ __global__ void __launch_bounds__(256) gemm_s3(SplitGemm G) {
     // exact; the first step's sign alternates between splits).  A gradient-like
     // 300,000 x 128 by 300,000 x 64, relative to float64: 8.3e-7 (mean -7.8e-7 of
     // the rms) without, 3.5e-7 (4e-9) with, 4.2e-7 on fp32 products; 640,000 x 256
-    // by 128 3.0e-6, 1.0e-6, 1.3e-6.  It costs 2 to 4%.  Over channels (at most
+    // by 128 3.0e-6, 1.0e-6, 1.3e-6.  It costs 2 to 6% (14% at 64 x 64 tiles: 76,800 x
+    // 256 by 43, 27.9 | 31.8 us, 37.5 on fp32 products).  Over channels (at most
     // 1,024 of them) the splits are nearer than fp32 products either way.
     constexpr bool ALT = !AKC;
     unsigned par = ALT ? (unsigned)blockIdx.z & 1u : 0u;
@@ -173,6 +175,11 @@ __global__ void __launch_bounds__(256) gemm_s3(SplitGemm G) {
         par ^= 1u;
     }
     if (ALT && par == 0u) negate();   // the last step's sign was 1
+    // Infinities and NaN do not survive a split (inf - inf in its parts), nor do
+    // values that round to an infinite bf16: outputs that are not finite are
+    // stored and then taken again, below.
+    auto finite = [](float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; };
+    bool redo = false;
     // lane l of block (j, i): row 16 i + l % 16, columns 16 j + 4 (l / 16) .. + 3
     float *C = G.C + (int64_t)blockIdx.z * G.c_split;
 #pragma unroll
@@ -183,6 +190,8 @@ __global__ void __launch_bounds__(256) gemm_s3(SplitGemm G) {
             const int64_t m = m0 + wm * (TM / WM) + i * 16 + (lane & 15);
             if (m >= G.M || n >= G.N) continue;
             float *p = C + m * G.ldc + n;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) redo |= !finite(acc[j][i][v]);
             if (G.cvec && n + 4 <= G.N) {
                 *reinterpret_cast<f4 *>(p) = acc[j][i];
             } else {
@@ -191,6 +200,23 @@ __global__ void __launch_bounds__(256) gemm_s3(SplitGemm G) {
                     if (n + v < G.N) p[v] = acc[j][i][v];
             }
         }
+    }
+    if (!redo) return;
+    // the lane's own outputs once more, those that are not finite as plain fp32
+    // sums (up to the first NaN, which stays)
+#pragma unroll 1
+    for (int e = 0; e < NJ * NI * 4; ++e) {
+        const int64_t m = m0 + wm * (TM / WM) + (e >> 2) % NI * 16 + (lane & 15);
+        const int64_t n = n0 + wn * (TN / WN) + (e >> 2) / NI * 16 + 4 * (lane >> 4) + (e & 3);
+        if (m >= G.M || n >= G.N || finite(C[m * G.ldc + n])) continue;
+        const int64_t row = G.row_map ? (int64_t)G.row_map[m] : m;
+        float s = 0.f;
+        for (int64_t k = kb; k < ke && s == s; ++k) {
+            const float a = row < 0 ? 0.f : G.A[AKC ? row * G.lda + k : k * G.lda + row];
+            const float b = n == G.ones_col ? 1.f : G.B[BKC ? n * G.ldb + k : k * G.ldb + n];
+            s = fmaf(a, b, s);
+        }
+        C[m * G.ldc + n] = s;
     }
 }
 

@@ -570,3 +570,40 @@ def test_encoder_non_finite_features_many_rows(f_op, f, dtype):
     assert not np.isfinite(many[0][5]).all() and not np.isfinite(many[0][100]).all()
     assert np.isfinite(many[0][6]).all()
     g.close()
+
+
+@pytest.mark.parametrize("f,H,row", [(64, 64, "op"), (128, 96, "op"), (128, 96, "dev"), (256, 128, "dev")])
+def test_decide_non_finite_embeddings_many_rows(f, H, row):
+    """An infinity or a NaN in one embedding row of a call of 8,192 query rows and of 8,192 device rows: the candidates
+    that read it get what the same queries get in a call of few rows, and the other candidates are as without it."""
+    R, m, Q = 1024, 8, 8192
+    topo = synth.random_topology(960 + f, 6, m, 8)
+    rng = np.random.default_rng((2302, 96, f, H))
+    E_op = rng.uniform(0, 1, (R, 6, f)).astype(np.float32)
+    E_dev = rng.uniform(0, 1, (R, m, f)).astype(np.float32)
+    w = synth.make_weights(f, 4, 1, 42, H, bias_scale=0.2, seed_extra=f)
+    masks = rng.integers(1, 1 << m, 40).astype(np.uint64)
+    opts = rng.integers(0, 4, 40).astype(np.uint8)
+    g = P.Graph([topo])
+    mod = P.Model(w, f=f, heads=4, layers=1, f_op=42, dec_hidden=H)
+    rep, op = np.repeat(np.arange(R), Q // R), rng.integers(0, 6, Q)
+    ask = lambda a, b, rs: P.decide(g, mod, dev_tensor(a[rs]), dev_tensor(b[rs]), masks, opts, rep[np.isin(rep, rs)] - rs[0],
+                                    np.zeros(np.isin(rep, rs).sum(), np.int32), op[np.isin(rep, rs)])
+    clean = ask(E_op, E_dev, np.arange(R))
+    bad = {3: np.inf, 500: -np.inf, 1023: np.nan}
+    for r, v in bad.items():
+        if row == "op":
+            E_op[r, :, f // 2] = v
+        else:
+            E_dev[r, :, 5] = v
+    many = ask(E_op, E_dev, np.arange(R))
+    keep = ~np.isin(rep, list(bad))
+    for k in ("prior", "best", "argmax"):
+        np.testing.assert_array_equal(many[k][keep], clean[k][keep])
+    for r in bad:
+        few = ask(E_op, E_dev, np.array([r]))
+        np.testing.assert_array_equal(many["argmax"][rep == r], few["argmax"])
+        np.testing.assert_array_equal(np.isfinite(many["prior"][rep == r]), np.isfinite(few["prior"]))
+        np.testing.assert_allclose(many["best"][rep == r], few["best"], rtol=1e-5, equal_nan=True)
+        np.testing.assert_allclose(many["prior"][rep == r], few["prior"], rtol=1e-4, atol=1e-7, equal_nan=True)
+    g.close()
