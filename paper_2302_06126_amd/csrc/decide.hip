@@ -203,7 +203,7 @@ __device__ __forceinline__ float slice_score(const DecArgs &A, const float *urg,
 }
 
 // argmax, best score and decoded decision of query q (topology g)
-__device__ void write_decision(const DecArgs &A, int32_t q, int32_t g, float M, int32_t best) {
+__device__ __forceinline__ void write_decision(const DecArgs &A, int32_t q, int32_t g, float M, int32_t best) {
     if (best < 0 || best >= A.S) {   // no comparable score (NaN inputs)
         A.argmax[q] = -1;
         A.best[q] = __builtin_nanf("");
@@ -225,8 +225,8 @@ __device__ void write_decision(const DecArgs &A, int32_t q, int32_t g, float M, 
 // Max (lowest index on ties) and sum of exponentials over the block's
 // per-thread partials, then the prior, argmax and decoded decision of query
 // q whose raw scores are already in A.prior (when it is given).
-__device__ void finish_query(const DecArgs &A, int32_t q, int32_t g, float m, int32_t im, float z,
-                             float *red_m, int32_t *red_i, float *red_z) {
+__device__ __forceinline__ void finish_query(const DecArgs &A, int32_t q, int32_t g, float m, int32_t im, float z,
+                                             float *red_m, int32_t *red_i, float *red_z) {
     red_m[threadIdx.x] = m; red_i[threadIdx.x] = im; red_z[threadIdx.x] = z;
     __syncthreads();
     for (int off = kScoreThreads / 2; off > 0; off >>= 1) {
@@ -254,7 +254,7 @@ __device__ void finish_query(const DecArgs &A, int32_t q, int32_t g, float m, in
     if (threadIdx.x == 0) write_decision(A, q, g, M, best);
 }
 
-__device__ void invalid_query(const DecArgs &A, int32_t q) {
+__device__ __forceinline__ void invalid_query(const DecArgs &A, int32_t q) {
     if (threadIdx.x == 0) {
         A.argmax[q] = -1;
         A.best[q] = __builtin_nanf("");
@@ -264,31 +264,28 @@ __device__ void invalid_query(const DecArgs &A, int32_t q) {
         for (int32_t a = threadIdx.x; a < A.S; a += blockDim.x) A.prior[(int64_t)q * A.S + a] = 0.f;
 }
 
-// queries q0 .. q0 + nq - 1 one by one (256 threads)
-__device__ void score_singly(const DecArgs &A, int32_t q0, int32_t nq, float *vq, const float *w2s, float *red_m,
-                             int32_t *red_i, float *red_z) {
-    for (int i = 0; i < nq; ++i) {
-        const int32_t q = q0 + i;
-        int32_t r, g, op;
-        if (!query_valid(A, q, &r, &g, &op)) {
-            invalid_query(A, q);
-            continue;
-        }
-        __syncthreads();   // the previous query's reads of v are done
-        for (int h = threadIdx.x; h < A.Hx; h += blockDim.x) vq[h] = A.v[(int64_t)q * A.Hx + h];
-        __syncthreads();
-        const float *urg = A.u + ((int64_t)r * A.G + g) * A.Hx * A.S;
-        // max (lowest index on ties) and the running sum of exponentials
-        float m = -INFINITY, z = 0.f;
-        int32_t im = INT32_MAX;
-        for (int32_t a = threadIdx.x; a < A.S; a += blockDim.x) {
-            float s = slice_score(A, urg, vq, w2s, a);
-            if (A.prior) A.prior[(int64_t)q * A.S + a] = s;
-            if (s > m) { z = z * __expf(m - s) + 1.f; m = s; im = a; }
-            else z += __expf(s - m);
-        }
-        finish_query(A, q, g, m, im, z, red_m, red_i, red_z);
+// one query by 256 threads (vq: Hx floats)
+__device__ __forceinline__ void score_one(const DecArgs &A, int32_t q, float *vq, const float *w2s, float *red_m,
+                                          int32_t *red_i, float *red_z) {
+    int32_t r, g, op;
+    if (!query_valid(A, q, &r, &g, &op)) {
+        invalid_query(A, q);
+        return;
     }
+    __syncthreads();   // a previous query's reads of v are done
+    for (int h = threadIdx.x; h < A.Hx; h += blockDim.x) vq[h] = A.v[(int64_t)q * A.Hx + h];
+    __syncthreads();
+    const float *urg = A.u + ((int64_t)r * A.G + g) * A.Hx * A.S;
+    // max (lowest index on ties) and the running sum of exponentials
+    float m = -INFINITY, z = 0.f;
+    int32_t im = INT32_MAX;
+    for (int32_t a = threadIdx.x; a < A.S; a += blockDim.x) {
+        float s = slice_score(A, urg, vq, w2s, a);
+        if (A.prior) A.prior[(int64_t)q * A.S + a] = s;
+        if (s > m) { z = z * __expf(m - s) + 1.f; m = s; im = a; }
+        else z += __expf(s - m);
+    }
+    finish_query(A, q, g, m, im, z, red_m, red_i, red_z);
 }
 
 // QB consecutive queries per block: scores, softmax prior, argmax, decoded
@@ -362,7 +359,7 @@ __global__ void __launch_bounds__(kScoreThreads) dec_score(DecArgs A) {
         for (int i = 0; i < QB; ++i) finish_query(A, q0 + i, gq[0], m[i], im[i], z[i], red_m, red_i, red_z);
         return;
     }
-    score_singly(A, q0, nq, sh, w2s, red_m, red_i, red_z);
+    for (int i = 0; i < nq; ++i) score_one(A, q0 + i, sh, w2s, red_m, red_i, red_z);
 }
 
 // kGroupQ consecutive queries per block, two slices and half of the hidden
@@ -420,7 +417,7 @@ __global__ void __launch_bounds__(kScoreThreads) dec_score_group(DecArgs A) {
         __syncthreads();
         float *w2s = sh + A.Hx;
         for (int h = threadIdx.x; h < H; h += kScoreThreads) w2s[h] = A.w2[h];
-        score_singly(A, q0, nq, sh, w2s, red_m, red_i, red_z);
+        for (int i = 0; i < nq; ++i) score_one(A, q0 + i, sh, w2s, red_m, red_i, red_z);
         return;
     }
     const float *urg = A.u + ((int64_t)r0 * A.G + g0) * A.Hx * A.S;
