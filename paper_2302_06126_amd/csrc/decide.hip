@@ -37,7 +37,7 @@ struct DecArgs {
     int32_t *argmax;
     float *best, *prior;
     tag_decision *dec;
-    int32_t bound;       // dec_slice leaves max_a |u[rg][h][a]| in t's row of rg's first device
+    int32_t bound;       // dec_slice leaves a bound of |u[rg][h][a]| over a in t's row of rg's first device
 };
 
 // u[rg][h][a] = sum_{j in mask_a} t[dev(rg, j)][h] + P[h][2F + opt_a] (+ b1[h])
@@ -64,9 +64,16 @@ __global__ void __launch_bounds__(256) dec_slice(DecArgs A) {
     }
     __syncthreads();
     const uint64_t keep = nd >= 64 ? ~0ull : ((1ull << nd) - 1ull);
-    int ub[kSliceH];   // bits of the largest |u| (as integers a NaN is the largest)
+    if (A.bound && threadIdx.x >= 192) {   // this block alone reads these eight columns of the graph's t rows
+        // a bound of |u| of each unit: lane l sums every eighth device of unit l % 8 (infinities and NaN stay)
+        const int l = threadIdx.x & 63, hh = l & 7;
+        float b = 0.f;
+        for (int j = l >> 3; j < nd; j += 8) b += fabsf(tl[j][hh]);
+        for (int o = 8; o < 64; o <<= 1) b += __shfl_xor(b, o, 64);
 #pragma unroll
-    for (int hh = 0; hh < kSliceH; ++hh) ub[hh] = 0;
+        for (int o = 0; o < 4; ++o) b += fabsf(po[o][hh]);
+        if (l < kSliceH && h0 + hh < A.Hx) A.t[((int64_t)r * A.n_dev + d0) * A.Hx + h0 + hh] = b;
+    }
     for (int32_t a = threadIdx.x; a < A.S; a += blockDim.x) {
         uint64_t m = A.mask[a] & keep;
         const int opt = min((int)A.option[a], 3);
@@ -83,27 +90,6 @@ __global__ void __launch_bounds__(256) dec_slice(DecArgs A) {
 #pragma unroll
         for (int hh = 0; hh < kSliceH; ++hh)
             if (h0 + hh < A.Hx) u[(int64_t)hh * A.S] = acc[hh];
-#pragma unroll
-        for (int hh = 0; hh < kSliceH; ++hh) ub[hh] = max(ub[hh], __float_as_int(fabsf(acc[hh])));
-    }
-    if (A.bound) {   // this block alone reads these eight columns of the graph's t rows
-        // maxima of the eight units over the wavefront: each exchange halves the
-        // units a lane holds, so lane l ends with unit 4 l0 + 2 l1 + l2 (its low bits)
-        __shared__ int bl[4][kSliceH];
-        const int l0 = threadIdx.x & 1, l1 = (threadIdx.x >> 1) & 1, l2 = (threadIdx.x >> 2) & 1;
-        int v4[4], v2[2];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v4[i] = max(l0 ? ub[4 + i] : ub[i], __shfl_xor(l0 ? ub[i] : ub[4 + i], 1, 64));
-#pragma unroll
-        for (int i = 0; i < 2; ++i) v2[i] = max(l1 ? v4[2 + i] : v4[i], __shfl_xor(l1 ? v4[i] : v4[2 + i], 2, 64));
-        int b = max(l2 ? v2[1] : v2[0], __shfl_xor(l2 ? v2[0] : v2[1], 4, 64));
-        for (int o = 8; o < 64; o <<= 1) b = max(b, __shfl_xor(b, o, 64));
-        if ((threadIdx.x & 63) < kSliceH) bl[threadIdx.x >> 6][4 * l0 + 2 * l1 + l2] = b;
-        __syncthreads();
-        const int hh = threadIdx.x;
-        if (hh < kSliceH && h0 + hh < A.Hx)
-            A.t[((int64_t)r * A.n_dev + d0) * A.Hx + h0 + hh] =
-                __int_as_float(max(max(bl[0][hh], bl[1][hh]), max(bl[2][hh], bl[3][hh])));
     }
 }
 
