@@ -349,80 +349,52 @@ __global__ void __launch_bounds__(kScoreThreads) dec_score(DecArgs A) {
 }
 
 // kGroupQ consecutive queries per block, two slices and half of the hidden
-// units per thread: for calls with many queries per candidate (a whole op group of each), where
-// re-reading u from L2 for every query and the vector pipe bound the readout.
-// The block's queries must read one candidate's u (else they go one by one, in
-// the way of dec_score).  Hidden unit h of the block is scaled by a
-// power of two that brings its pre-activations into [-1, 1] (bound: max |u|
-// left by dec_slice plus max |v|), its readout weight by the inverse, both
-// exactly, so the ReLU is the clamp of one multiply-add and a (slice, query,
-// unit) costs two instructions, with the same bits; v and the weights are LDS
-// broadcasts, shared by the thread's two slices.  Scores meet in LDS, and each
-// wavefront finishes half of the queries.  42,496 queries, 256 slices, H = 256:
-// dec_score<4> 346 us (add, max, multiply-add; 2.8 GB of u reads from L2), this 240 us
-// plus 4 us in dec_slice for the bounds (vector issue: 162 us).
+// units per thread: for calls with many queries, where re-reading u from L2 for
+// every query and the vector pipe bound the readout.  The block's queries go
+// by runs that read one candidate's u (of up to four or up to eight), so every u
+// value is loaded once per run; a query that shares its u with no neighbour goes
+// the way of dec_score.
+// Hidden unit h of a run is scaled by a power of two that brings its
+// pre-activations into [-1, 1] (bound: max |u| left by dec_slice plus max |v|),
+// its readout weight by the inverse, both exactly, so the ReLU is the clamp of
+// one multiply-add and a (slice, query, unit) costs two instructions, with the
+// same bits; v and the weights are LDS broadcasts, shared by the thread's two
+// slices.  Scores meet in LDS, and each wavefront finishes a quarter of the
+// queries.
+// 42,496 queries of 256 candidates, 256 slices, H = 256: dec_score<4> 336 us (add,
+// max, multiply-add; 2.8 GB of u reads from L2), this 226 us plus 2 us in
+// dec_slice for the bounds (vector issue: 162 us).  Whole calls, dec_score<4> | this:
+// runs of 166 416 | 282 us, of 9 675 | 440, of 4 527 | 492, in random order 1,509 |
+// 1,501; 8,192 queries of 1,024 candidates, H = 128: runs of 40 100 | 84, of 12 98 |
+// 90, of 9 123 | 99, of 5 145 | 111, of 4 111 | 102, of 1 204 | 207, random 198 | 201.
 constexpr int kGroupQ = 8;
 constexpr int kGroupMinQ = 8192;                     // blocks to fill the chip (1,024 of them)
 constexpr int kGroupMaxH = 512, kGroupMaxS = 512;    // 20 + 16 KiB of LDS: four blocks per CU
 
-__global__ void __launch_bounds__(kScoreThreads) dec_score_group(DecArgs A) {
-    extern __shared__ __attribute__((aligned(16))) float sh[];   // v [H][8] | (2^-e, 2^e w2) [H][2] | scores [8][S]
-    __shared__ float red_m[kScoreThreads], red_z[kScoreThreads];
-    __shared__ int32_t red_i[kScoreThreads];
-    const int32_t q0 = (int32_t)xcd_swizzle(blockIdx.x, gridDim.x) * kGroupQ;
-    const int32_t nq = min(kGroupQ, A.Q - q0);
-    const int H = A.H;
-    int32_t r0 = 0, g0 = 0, op;
-    bool shared = query_valid(A, q0, &r0, &g0, &op);
-    for (int i = 1; i < nq; ++i) {
-        int32_t r, g;
-        shared = query_valid(A, q0 + i, &r, &g, &op) && shared && r == r0 && g == g0;
-    }
-    float *sv = sh, *sc = sh + kGroupQ * H, *ss = sc + 2 * H;
-    bool ok = true;
-    if (shared) {
-        const float *ub = A.t + ((int64_t)r0 * A.n_dev + A.dev_off[g0]) * A.Hx;
-        for (int h = threadIdx.x; h < H; h += kScoreThreads) {
-            float v[kGroupQ], b = ub[h], vm = 0.f;
-#pragma unroll
-            for (int i = 0; i < kGroupQ; ++i) {   // (a last group short of queries repeats its last one)
-                v[i] = A.v[(int64_t)(q0 + min(i, nq - 1)) * A.Hx + h];
-                vm += fabsf(v[i]);
-            }
-            const float w2 = A.w2[h];
-            b += vm;
-            ok = ok && relu_scalable(b, w2);
-            const int e = relu_exponent(b);
-#pragma unroll
-            for (int i = 0; i < kGroupQ; ++i) sv[h * kGroupQ + i] = ldexpf(v[i], -e);
-            sc[2 * h] = ldexpf(1.f, -e);
-            sc[2 * h + 1] = ldexpf(w2, e);
-        }
-    }
-    if (!__syncthreads_and(ok && shared)) {
-        __syncthreads();
-        float *w2s = sh + A.Hx;
-        for (int h = threadIdx.x; h < H; h += kScoreThreads) w2s[h] = A.w2[h];
-        for (int i = 0; i < nq; ++i) score_one(A, q0 + i, sh, w2s, red_m, red_i, red_z);
-        return;
-    }
-    const float *urg = A.u + ((int64_t)r0 * A.G + g0) * A.Hx * A.S;
+// scores of a run's queries 0 .. n - 1 (n <= NQ; v holds NQ) into ss [n][S]; v
+// [H][NQ] scaled, sc [H]: (2^-e, 2^e w2)
+template <int NQ>
+__device__ __forceinline__ void group_scores(const DecArgs &A, const float *urg, const float *sv, const float *sc,
+                                             float *ss, int n) {
+    const int S = A.S, H = A.H;
     const float b2 = A.b2[0];
-    const int S = A.S;
     const int half = threadIdx.x >> 7, hb = half ? H / 2 : 0, he = half ? H : H / 2;
     for (int32_t a0 = 0; a0 < S; a0 += kScoreThreads) {
         const int32_t a = a0 + (threadIdx.x & 127);
         const float *ua = urg + min(a, S - 1), *uc = urg + min(a + 128, S - 1);
-        float s[2][kGroupQ];
+        float s[2][NQ];
 #pragma unroll
-        for (int i = 0; i < kGroupQ; ++i) s[0][i] = s[1][i] = 0.f;
+        for (int i = 0; i < NQ; ++i) s[0][i] = s[1][i] = 0.f;
         auto unit = [&](int h, float u0, float u1) {
             const float2 c = *reinterpret_cast<const float2 *>(sc + 2 * h);
-            const float4 va = *reinterpret_cast<const float4 *>(sv + h * kGroupQ);
-            const float4 vb = *reinterpret_cast<const float4 *>(sv + h * kGroupQ + 4);
-            const float v[kGroupQ] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
+            float v[NQ];
 #pragma unroll
-            for (int i = 0; i < kGroupQ; ++i) {
+            for (int i = 0; i < NQ; i += 4) {
+                const float4 x = *reinterpret_cast<const float4 *>(sv + h * NQ + i);
+                v[i] = x.x; v[i + 1] = x.y; v[i + 2] = x.z; v[i + 3] = x.w;
+            }
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) {
                 s[0][i] = fmaf(c.y, clamp01(fmaf(u0, c.x, v[i])), s[0][i]);
                 s[1][i] = fmaf(c.y, clamp01(fmaf(u1, c.x, v[i])), s[1][i]);
             }
@@ -438,23 +410,96 @@ __global__ void __launch_bounds__(kScoreThreads) dec_score_group(DecArgs A) {
         for (; h < he; ++h) unit(h, ua[(int64_t)h * S], uc[(int64_t)h * S]);
         if (half) {
 #pragma unroll
-            for (int i = 0; i < kGroupQ; ++i) {
-                if (a < S) ss[i * S + a] = s[0][i];
-                if (a + 128 < S) ss[i * S + a + 128] = s[1][i];
+            for (int i = 0; i < NQ; ++i) {
+                if (i < n && a < S) ss[i * S + a] = s[0][i];
+                if (i < n && a + 128 < S) ss[i * S + a + 128] = s[1][i];
             }
         }
         __syncthreads();
         if (!half) {
 #pragma unroll
-            for (int i = 0; i < kGroupQ; ++i) {
-                if (a < S) ss[i * S + a] += s[0][i] + b2;
-                if (a + 128 < S) ss[i * S + a + 128] += s[1][i] + b2;
+            for (int i = 0; i < NQ; ++i) {
+                if (i < n && a < S) ss[i * S + a] += s[0][i] + b2;
+                if (i < n && a + 128 < S) ss[i * S + a + 128] += s[1][i] + b2;
             }
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kScoreThreads) dec_score_group(DecArgs A) {
+    extern __shared__ __attribute__((aligned(16))) float sh[];   // v [H][8] | (2^-e, 2^e w2) [H][2] | scores [8][S]
+    __shared__ float red_m[kScoreThreads], red_z[kScoreThreads];
+    __shared__ int32_t red_i[kScoreThreads], sr[kGroupQ], sg[kGroupQ];
+    const int32_t q0 = (int32_t)xcd_swizzle(blockIdx.x, gridDim.x) * kGroupQ;
+    const int32_t nq = min(kGroupQ, A.Q - q0);
+    const int H = A.H, S = A.S;
+    if ((int)threadIdx.x < nq) {
+        int32_t r, g, op;
+        const bool ok = query_valid(A, q0 + threadIdx.x, &r, &g, &op);
+        sr[threadIdx.x] = ok ? r : -1;
+        sg[threadIdx.x] = g;
+    }
+    float *sv = sh, *sc = sh + kGroupQ * H, *ss = sc + 2 * H;
+    float *w2s = sh + H;   // of queries that go alone, after their v
+    bool w2_in = false;
+    uint32_t done = 0;     // queries that are finished already
+    for (int i0 = 0, n; i0 < nq; i0 += n) {
+        __syncthreads();   // the queries are known, and the last run's reads of v are done
+        const int32_t r = __builtin_amdgcn_readfirstlane(sr[i0]), g = __builtin_amdgcn_readfirstlane(sg[i0]);
+        n = 1;
+        if (r < 0) {
+            invalid_query(A, q0 + i0);
+            done |= 1u << i0;
+            continue;
+        }
+        while (i0 + n < nq && sr[i0 + n] == r && sg[i0 + n] == g) ++n;
+        n = __builtin_amdgcn_readfirstlane(n);
+        if (n == 1) {   // nothing to share: as dec_score does
+            if (!w2_in)
+                for (int h = threadIdx.x; h < H; h += kScoreThreads) w2s[h] = A.w2[h];
+            w2_in = true;
+            score_one(A, q0 + i0, sh, w2s, red_m, red_i, red_z);
+            done |= 1u << i0;
+            continue;
+        }
+        w2_in = false;   // (v takes its place)
+        const int nv = n <= 4 ? 4 : 8;
+        const float *ub = A.t + ((int64_t)r * A.n_dev + A.dev_off[g]) * A.Hx;
+        bool ok = true;
+        for (int h = threadIdx.x; h < H; h += kScoreThreads) {
+            const float *vq = A.v + (int64_t)(q0 + i0) * A.Hx + h;
+            float v[kGroupQ], b = ub[h], vm = 0.f;
+#pragma unroll
+            for (int i = 0; i < kGroupQ; ++i) {   // (past the run: its last query again)
+                v[i] = vq[(int64_t)min(i, n - 1) * A.Hx];
+                vm = i < n ? vm + fabsf(v[i]) : vm;
+            }
+            const float w2 = A.w2[h];
+            b += vm;
+            ok = ok && relu_scalable(b, w2);
+            const int e = relu_exponent(b);
+#pragma unroll
+            for (int i = 0; i < kGroupQ; ++i)
+                if (i < nv) sv[h * nv + i] = ldexpf(v[i], -e);
+            sc[2 * h] = ldexpf(1.f, -e);
+            sc[2 * h + 1] = ldexpf(w2, e);
+        }
+        const float *urg = A.u + ((int64_t)r * A.G + g) * A.Hx * S;
+        if (!__syncthreads_and(ok)) {   // infinities, NaN, huge values: ReLU as a max
+            for (int h = threadIdx.x; h < H; h += kScoreThreads) w2s[h] = A.w2[h];
+            w2_in = true;
+            for (int i = 0; i < n; ++i) score_one(A, q0 + i0 + i, sh, w2s, red_m, red_i, red_z);
+            done |= ((1u << n) - 1u) << i0;
+        } else if (n <= 4) {
+            group_scores<4>(A, urg, sv, sc, ss + i0 * S, n);
+        } else {
+            group_scores<8>(A, urg, sv, sc, ss + i0 * S, n);
         }
     }
     __syncthreads();
     const int lane = threadIdx.x & 63;
     for (int i = threadIdx.x >> 6; i < nq; i += kScoreThreads / 64) {
+        if ((done >> i) & 1u) continue;
         const int32_t q = q0 + i;
         float m = -INFINITY;
         int32_t im = INT32_MAX;
@@ -476,7 +521,7 @@ __global__ void __launch_bounds__(kScoreThreads) dec_score_group(DecArgs A) {
             const float inv = 1.f / z;
             for (int32_t a = lane; a < S; a += 64) A.prior[(int64_t)q * S + a] = ss[i * S + a] * inv;
         }
-        if (lane == 0) write_decision(A, q, g0, m, im);
+        if (lane == 0) write_decision(A, q, sg[i], m, im);
     }
 }
 
@@ -574,7 +619,8 @@ tag_status decide_run(const tag_graph *g, const tag_model_dims *dims, const tag_
     prof_begin(TAG_STAGE_DECIDE, stream);
     launch_projections(A, L.qrow, stream);
     dec_slice<<<(unsigned)((int64_t)A.R * A.G * ((Hx + kSliceH - 1) / kSliceH)), 256, 0, stream>>>(A);
-    // eight or four queries per block once there are enough blocks to fill the GPU
+    // eight or four queries per block once there are enough blocks to fill the GPU (four: wider
+    // heads and tables than dec_score_group's LDS holds, and the linear head)
     if (group)
         dec_score_group<<<(unsigned)((A.Q + kGroupQ - 1) / kGroupQ), kScoreThreads,
                           sizeof(float) * ((kGroupQ + 2) * Hx + kGroupQ * A.S), stream>>>(A);

@@ -607,3 +607,41 @@ def test_decide_non_finite_embeddings_many_rows(f, H, row):
         np.testing.assert_allclose(many["best"][rep == r], few["best"], rtol=1e-5, equal_nan=True)
         np.testing.assert_allclose(many["prior"][rep == r], few["prior"], rtol=1e-4, atol=1e-7, equal_nan=True)
     g.close()
+
+
+@pytest.mark.parametrize("f,H,S,runs", [(64, 64, 60, (1, 2)), (128, 128, 256, (3, 6)), (64, 37, 300, (1, 12)),
+                                        (128, 512, 512, (4, 5)), (64, 64, 33, (1, 1))])
+def test_decide_runs_within_a_group(f, H, S, runs):
+    """8,195 queries in runs of given lengths per candidate, so that the groups of eight hold one run, several or none:
+    the same as in calls too short for groups.  One candidate's values are past the range that is scaled, one's are
+    not finite, and some queries are invalid."""
+    R, m, n, Q = 300, 6, 7, 8195
+    topo = synth.random_topology(970 + H, n, m, 9)
+    rng = np.random.default_rng((2302, 97, f, H, S))
+    E_op = rng.uniform(0, 1, (R, n, f)).astype(np.float32)
+    E_dev = rng.uniform(0, 1, (R, m, f)).astype(np.float32)
+    E_dev[17] *= np.float32(1e14)
+    E_op[40, 3, 5] = np.nan
+    w = synth.make_weights(f, 4, 1, 42, H, bias_scale=0.2, seed_extra=f)
+    masks = rng.integers(1, 1 << m, S).astype(np.uint64)
+    opts = rng.integers(0, 4, S).astype(np.uint8)
+    g = P.Graph([topo])
+    mod = P.Model(w, f=f, heads=4, layers=1, f_op=42, dec_hidden=H)
+    length = rng.integers(runs[0], runs[1] + 1, Q)
+    qr = np.repeat(rng.integers(0, R, Q), length)[:Q].astype(np.int32)
+    qo = rng.integers(0, n, Q).astype(np.int32)
+    qo[rng.choice(Q, 20, replace=False)] = n
+    d_op, d_dev = dev_tensor(E_op), dev_tensor(E_dev)
+    many = P.decide(g, mod, d_op, d_dev, masks, opts, qr, np.zeros(Q, np.int32), qo)
+    parts = [P.decide(g, mod, d_op, d_dev, masks, opts, qr[s], np.zeros(len(qr[s]), np.int32), qo[s])
+             for s in (slice(0, 4000), slice(4000, 8000), slice(8000, Q))]
+    few = {k: np.concatenate([p[k] for p in parts]) for k in many}
+    # (sums in another order: scores that lie apart by rounding may swap)
+    s2 = np.sort(np.nan_to_num(few["prior"], nan=0.0), axis=1)
+    apart = (s2[:, -1] - s2[:, -2] > 1e-4 * s2[:, -1]) | (few["argmax"] < 0) | (qr == 40)
+    np.testing.assert_array_equal(many["argmax"][apart], few["argmax"][apart])
+    np.testing.assert_allclose(many["best"], few["best"], rtol=2e-5, atol=1e-5, equal_nan=True)
+    ok = qr != 17   # (scores of 1e14: their differences are rounding)
+    np.testing.assert_allclose(many["prior"][ok], few["prior"][ok], rtol=2e-4, atol=1e-7, equal_nan=True)
+    assert (many["argmax"][qo == n] == -1).all() and (many["prior"][qo == n] == 0).all()
+    g.close()
