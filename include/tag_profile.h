@@ -35,9 +35,10 @@ enum {
     /* tag_train_step (include/tag_train.h); its forward pass records the   */
     /* stages above                                                         */
     TAG_STAGE_BWD_DECODER = 9,    /* decoder loss + backward kernels (one pair per call)     */
-    TAG_STAGE_BWD_SCORES = 10,    /* per-entry scores, one launch per bucket (4/layer)       */
-    TAG_STAGE_BWD_SOFTMAX = 11,   /* per-destination softmax backward (4/layer)              */
-    TAG_STAGE_BWD_MESSAGES = 12,  /* per-source message backward (4/layer)                   */
+    TAG_STAGE_BWD_SCORES = 10,    /* per-entry scores, one launch per bucket (4/layer; 3 where */
+                                  /* the op-device tile kernels take two of them)            */
+    TAG_STAGE_BWD_SOFTMAX = 11,   /* per-destination softmax backward (likewise)             */
+    TAG_STAGE_BWD_MESSAGES = 12,  /* per-source message backward (likewise)                  */
     TAG_STAGE_BWD_DH = 13,        /* dH = dY W GEMMs, op and device rows (2/layer)           */
     TAG_STAGE_BWD_DW = 14,        /* split-K dW^h = dY^T H GEMMs (2/layer)                   */
     TAG_STAGE_COUNT = 15

@@ -55,7 +55,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int GM = 64, GN = 64, GK = 32;   // output tile and k-step the splits over K are counted in
 
 // split count for a k-range of K rows over `tiles` output tiles: enough
-// blocks to fill the chip, at least 4 k-chunks per split
+// blocks to fill the chip, at least about two k-steps per split
 int64_t split_k_per(int64_t K, int64_t tiles, int64_t *splits) {
     int64_t s = std::max<int64_t>(1, std::min<int64_t>(1024 / std::max<int64_t>(tiles, 1), (K + 63) / 64));
     int64_t per = ((K + s - 1) / s + GK - 1) / GK * GK;
@@ -1876,8 +1876,25 @@ size_t od_messages_lds(int K, int max_dev) {
 
 // The op-device tile path takes what the forward pass's tile path takes (its
 // op masks are read here): heads of at least 16 channels, at most 16 heads;
-// a topology has at most 64 devices.
-bool od_tiles_fit(const tag_graph *g, const FwdLayout &fl) { return g->n_tiles > 0 && fl.mfma; }
+// a topology has at most 64 devices.  Its products are dense over (op, device)
+// in blocks of 16 devices, one head after the other, where the passes over the
+// links cost by the link (and by the length of the device rows), so few links on
+// many devices are left to those.  With one device block: tiles always.  With
+// two, three and four: from 0.15, 0.25 and 1 (K + 1) links per op and 4 K links
+// per device and device block on.  A step of two layers, links | tiles, us: 8
+// candidates of 6,000 ops, f = 128, K = 8, 64 devices: 1 link per op 1,755 | 2,269,
+// 4 1,968 | 2,345, 16 3,000 | 2,390; 48 devices: 1 1,645 | 1,743, 4 1,903 | 1,763;
+// 32 devices: 1 1,598 | 1,520; f = 256, K = 16, 64 devices: 4 3,326 | 4,369, 16 5,071 |
+// 4,474; 32 devices: 1 2,735 | 2,801, 4 3,234 | 2,834; f = 64, K = 4, 64 devices: 4
+// 1,397 | 1,474, 16 2,132 | 1,491.  400 ops, f = 128, 64 devices: K = 4, 8 897 | 974
+// (4: 866 | 987), 16 1,043 | 962; K = 8, 16 1,094 | 1,130.  1,200 ops, 16 devices: 1
+// 680 | 535.
+bool od_tiles_fit(const tag_graph *g, const tag_model_dims *d, const FwdLayout &fl) {
+    constexpr int kWeight[4] = {0, 3, 5, 20};   // twentieths, by device blocks
+    const int64_t blocks = (std::max(g->max_dev, 1) + 15) / 16, K = d->heads;
+    if (g->n_tiles <= 0 || !fl.mfma) return false;
+    return blocks == 1 || (20 * g->e_od >= kWeight[blocks - 1] * (K + 1) * g->n_op && g->e_od >= 4 * K * blocks * g->n_dev);
+}
 
 int32_t persist_blocks(int64_t items) {
     return (int32_t)std::max<int64_t>(1, std::min<int64_t>(kPersist, (items + 3) / 4));
@@ -1909,6 +1926,7 @@ size_t carve_train(const tag_graph *g, const tag_model_dims *d, int32_t R, int32
     L->fwd = c.take<char>(fb);
     L->fwd_bytes = fb;
     const int64_t F = d->f, K = d->heads, ro = (int64_t)R * g->n_op, rd = (int64_t)R * g->n_dev;
+    const bool tiles = od_tiles_fit(g, d, fl);
     for (int l = 0; l < 16; ++l) L->H_op[l] = L->H_dev[l] = L->Y_op[l] = L->Y_dev[l] = nullptr;
     for (int l = 0; l < d->layers; ++l) {
         L->H_op[l] = c.take<float>(ro * F);
@@ -1942,7 +1960,7 @@ size_t carve_train(const tag_graph *g, const tag_model_dims *d, int32_t R, int32
         L->part_a[b] = c.take<float>((size_t)L->nb_a[b] * F);
         L->part_m[b] = c.take<float>((size_t)4 * L->nb_m[b] * F);
     }
-    if (od_tiles_fit(g, fl)) {
+    if (tiles) {
         const int64_t nb = (int64_t)R * g->n_tiles;
         L->PD = c.take<float>((size_t)nb * g->max_dev * F);
         L->part_od = c.take<float>((size_t)4 * nb * F);

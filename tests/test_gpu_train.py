@@ -24,6 +24,7 @@ pytestmark = pytest.mark.gpu
 GRAD_TOL = 1e-3
 GRAD_FLOOR = 2e-6
 LOSS_TOL = 2e-5
+TAG_STAGE_BWD_SCORES = 10   # tag_profile.h
 
 
 def _say(msg):
@@ -156,11 +157,11 @@ def test_train_step_matches_reference_union_of_topologies(torch, f, heads, layer
     _say(f"[train] union: worst relative gradient error {max(worst.values()):.2e}")
 
 
-@pytest.mark.parametrize("f,heads,sizes", [(64, 4, [(65, 16, 3), (130, 17, 5)]),      # one and two device blocks
-                                           (128, 8, [(64, 32, 32), (70, 5, 2)]),      # a full second block; a small one
+@pytest.mark.parametrize("f,heads,sizes", [(64, 4, [(129, 16, 9), (130, 17, 5)]),     # one and two device blocks
+                                           (128, 8, [(128, 32, 32), (70, 5, 2)]),     # a full second block; a small one
                                            (256, 4, [(129, 33, 33), (3, 1, 1)]),      # three blocks; one op, one device
-                                           (256, 1, [(66, 48, 7)]), (64, 1, [(1, 64, 64), (190, 49, 4)]),
-                                           (256, 16, [(130, 64, 64)])])               # four blocks, narrowest heads
+                                           (256, 1, [(130, 48, 7)]), (64, 1, [(1, 64, 64), (450, 49, 4)]),
+                                           (256, 16, [(258, 64, 64)])])               # four blocks, narrowest heads
 def test_train_step_device_blocks(torch, f, heads, sizes):
     """The op-device tile kernels over one to four blocks of 16 devices: edges
     of a block, full and sparse placements, ragged op tiles, unlike topologies
@@ -169,13 +170,34 @@ def test_train_step_device_blocks(torch, f, heads, sizes):
              for i, (n, m, od) in enumerate(sizes)]
     c = TrainCase(topos, 2, f, heads, 2, 24, 2, seed=f + heads + len(sizes))
     graph, model, tr, feats = c.trainer(torch)
+    assert P.tag_profile_begin(TAG_STAGE_BWD_SCORES, 16) == 0
     loss = float(tr.step(feats).cpu()[0])
+    assert P.tag_profile_end()[2] == 6        # three score launches a layer: the tile kernels
     ref_loss, ref_g = c.reference()
     worst = _compare(tr, loss, ref_loss, ref_g, c.w)
     _say(f"[train] device blocks f={f} K={heads} {sizes}: worst relative gradient error {max(worst.values()):.2e}")
     g1 = {k: v.clone() for k, v in tr.grads.items()}
     tr.step(feats)
     assert all(torch.equal(g1[k], tr.grads[k]) for k in OT.PARAMS)
+
+
+@pytest.mark.parametrize("f,heads,n_op,n_dev,od,tiles", [
+    (64, 4, 1400, 64, 4, False), (64, 4, 820, 64, 5, True), (64, 4, 819, 64, 5, False),   # links per op; per device
+    (256, 16, 300, 48, 13, False), (256, 16, 400, 33, 16, True), (128, 8, 1800, 48, 2, False), (128, 8, 1600, 48, 3, True),
+    (256, 16, 1000, 17, 2, False), (256, 16, 800, 17, 3, True), (64, 1, 140, 17, 1, True), (256, 16, 70, 16, 1, True)])
+def test_train_step_links_per_op(torch, f, heads, n_op, n_dev, od, tiles):
+    """Few links on many devices take the passes over the links, more the tile kernels over all devices: both sides of
+    the line, with the route read from the number of score launches (four, or three with tiles)."""
+    topo = synth.random_topology(50 + n_dev, n_op, n_dev, 90, od_per_op=od, dd_density=0.3)
+    c = TrainCase([topo], 1, f, heads, 1, 24, 2, seed=f + heads + od)
+    graph, model, tr, feats = c.trainer(torch)
+    assert P.tag_profile_begin(TAG_STAGE_BWD_SCORES, 16) == 0
+    loss = float(tr.step(feats).cpu()[0])
+    st, _, launches = P.tag_profile_end()
+    assert st == 0 and launches == (3 if tiles else 4)
+    ref_loss, ref_g = c.reference()
+    worst = _compare(tr, loss, ref_loss, ref_g, c.w)
+    _say(f"[train] f={f} K={heads} {od} of {n_dev} devices: worst relative gradient error {max(worst.values()):.2e}")
 
 
 def test_train_step_repeatable_and_sgd_update(torch):
