@@ -1941,8 +1941,9 @@ size_t carve_train(const tag_graph *g, const tag_model_dims *d, int32_t R, int32
     L->dY_op = c.take<float>(ro * 2 * F);
     L->dY_dev = c.take<float>(rd * 2 * F);
     for (int b = 0; b < 4; ++b) {
-        L->SA[b] = c.take<float>((size_t)R * n_slots(g, b) * K);
-        L->SD[b] = c.take<float>((size_t)R * n_slots(g, b) * K);
+        const bool own = !(tiles && b == 1);   // (the tile kernels keep op<-device scalars on chip)
+        L->SA[b] = own ? c.take<float>((size_t)R * n_slots(g, b) * K) : nullptr;
+        L->SD[b] = own ? c.take<float>((size_t)R * n_slots(g, b) * K) : nullptr;
     }
     L->Zop = c.take<float>(ro * 2 * K);
     L->Zdev = c.take<float>(rd * 2 * K);
@@ -1950,7 +1951,7 @@ size_t carve_train(const tag_graph *g, const tag_model_dims *d, int32_t R, int32
     for (int b = 0; b < 4; ++b) {
         const int64_t rows = (b < 2) ? ro : rd;
         const int32_t ch = chunks_of(g->max_degree[b], kChunkB);
-        if (ch > 1) pb = std::max(pb, rows * ch * F);
+        if (ch > 1 && !(tiles && (b == 1 || b == 2))) pb = std::max(pb, rows * ch * F);
     }
     L->PB = c.take<float>(std::max<int64_t>(pb, 1));
     for (int b = 0; b < 4; ++b) {
@@ -1977,8 +1978,8 @@ size_t carve_train(const tag_graph *g, const tag_model_dims *d, int32_t R, int32
         L->nb_dev4 = 0;
         L->dev_topo = nullptr;
     }
-    L->pos_of = c.take<int32_t>((size_t)std::max<int64_t>(g->e_od, 1));
-    L->m21 = c.take<int32_t>((size_t)std::max<int64_t>(g->e_od, 1));
+    L->pos_of = tiles ? nullptr : c.take<int32_t>((size_t)std::max<int64_t>(g->e_od, 1));
+    L->m21 = tiles ? nullptr : c.take<int32_t>((size_t)std::max<int64_t>(g->e_od, 1));
     L->dU = c.take<float>((size_t)d->layers * 3 * F * 2);
     L->dcp = c.take<float>((size_t)d->layers * 3 * F);
     const int64_t sp = split_floats(g, d, R, Q);
