@@ -73,3 +73,26 @@ def test_work_model_counts_records_and_table(name):
     t = R * M * F * (12 if (wl.dtype == "bf16" or F >= 256) else 8)
     assert by_prep == pytest.approx(R * (N + M) * 2 * F * s + t + R * (N + M) * 4 * K * 4)
     assert math.isfinite(by_merge) and by_merge > rec
+
+
+@pytest.mark.parametrize("f,bound", [(64, "hbm"), (128, "hbm"), (256, "mfma")])
+def test_training_products_are_priced_on_their_bf16_splits(f, bound):
+    # dH: 4 f^2 flop and 12 f bytes a row, f / 3 flop per byte against the split peak's ridge of 52
+    rows = 1e6
+    flops, byts = 4 * rows * f * f, 12 * rows * f
+    roof = bench.train_roof("bwd_dh", flops, byts, 1e-3)
+    assert roof["bound"] == bound
+    if bound == "mfma":
+        assert roof["peak"] == pytest.approx(416.67, abs=0.01)
+        assert roof["frac"] == pytest.approx(flops / 1e-3 / 1e12 / (2500.0 / 6), abs=1e-4)
+    assert bench.train_roof("bwd_scores", flops, byts, 1e-3)["bound"] == "hbm"
+    assert all("gemm_f32" not in v for v in bench.TRAIN_KERNELS.values())
+
+
+@pytest.mark.parametrize("name", ["cnn", "large"])
+def test_encode_bytes_hold_the_whole_stage(name):
+    wl, topo, (_, byts) = _work(name, "encode")
+    N, M, F, R = topo.n_op, topo.n_dev, wl.f, wl.batch
+    rows = R * (N * wl.f_op + M * 8) * 4 + R * (N + M) * F * (2 if wl.dtype == "bf16" else 4)
+    assert byts >= rows + R * topo.e_od + R * N * 16
+    assert byts <= rows + R * topo.e_od + R * N * 16 + 64 * (topo.e_od + topo.e_oo + N) + 16 * wl.layers * 3 * F * F
