@@ -223,8 +223,9 @@ __global__ void __launch_bounds__(256) gemm_s3(SplitGemm G) {
 template <int TM, int TN>
 void launch_tile(const SplitGemm &G, bool a_kc, bool b_kc, int64_t splits, hipStream_t st) {
     const dim3 grid((unsigned)((G.M + TM - 1) / TM), (unsigned)((G.N + TN - 1) / TN), (unsigned)splits);
-    if (!a_kc) gemm_s3<TM, TN, false, false><<<grid, 256, 0, st>>>(G);
-    else if (b_kc) gemm_s3<TM, TN, true, true><<<grid, 256, 0, st>>>(G);
+    if (!a_kc) {   // (sums over rows come in a few hundred 64-row tiles)
+        if constexpr (TM == 64) gemm_s3<TM, TN, false, false><<<grid, 256, 0, st>>>(G);
+    } else if (b_kc) gemm_s3<TM, TN, true, true><<<grid, 256, 0, st>>>(G);
     else gemm_s3<TM, TN, true, false><<<grid, 256, 0, st>>>(G);
 }
 
@@ -240,7 +241,7 @@ void launch_split_gemm(SplitGemm G, bool a_kc, bool b_kc, int64_t splits, hipStr
     G.cvec = al16(G.C, G.ldc) && G.c_split % 4 == 0;
     const int64_t b128 = ((G.M + 127) / 128) * ((G.N + 127) / 128) * splits;
     if (G.N <= 64) launch_tile<64, 64>(G, a_kc, b_kc, splits, st);
-    else if (G.M <= 64 || b128 < 768) launch_tile<64, 128>(G, a_kc, b_kc, splits, st);
+    else if (!a_kc || G.M <= 64 || b128 < 768) launch_tile<64, 128>(G, a_kc, b_kc, splits, st);
     else launch_tile<128, 128>(G, a_kc, b_kc, splits, st);
 }
 

@@ -502,7 +502,7 @@ def test_op_tile_parts_and_whole_tiles(f, heads, dtype, sigma):
                                              (64, 4, "relu", 985), (128, 4, "relu", 3), (256, 4, "elu", 1)])
 def test_fp32_transform_block_shapes(f, heads, sigma, R):
     """65 ops and 2 devices: 128 x 128 blocks of the fp32 relation transform from 512 of them on, 64 x 64 below
-    (985 replicas at f = 64: the last count below; 1 and 3: a ragged first block)."""
+    (974, 486 and 242 replicas at f = 64, 128 and 256: the last counts below; 1 and 3: a ragged first block)."""
     n, m = 65, 2
     rng = np.random.default_rng((2302, 93, f, heads, R))
     topo = mk_topo(n, m, oo=[(i, i + 1) for i in range(n - 1)], dd=[(0, 1)])
@@ -569,6 +569,26 @@ def test_encoder_non_finite_features_many_rows(f_op, f, dtype):
             np.testing.assert_array_equal(a[r:r + 1], b)
     assert not np.isfinite(many[0][5]).all() and not np.isfinite(many[0][100]).all()
     assert np.isfinite(many[0][6]).all()
+    g.close()
+
+
+def test_decide_projection_of_many_queries():
+    """49,153 queries at f = H = 256: the query projection's 128 x 128 blocks with a last one of one row."""
+    topo, R, E_op, E_dev, w, masks, opts = _decide_case(9, 256, 256, 40, 98)
+    g = P.Graph([topo])
+    m = P.Model(w, f=256, heads=4, layers=1, f_op=42, dec_hidden=256)
+    rng = np.random.default_rng(98)
+    Q = 49153
+    qr = np.sort(rng.integers(0, R, Q)).astype(np.int32)
+    qo = rng.integers(0, topo.n_op, Q).astype(np.int32)
+    res = P.decide(g, m, dev_tensor(E_op), dev_tensor(E_dev), masks, opts, qr, np.zeros(Q, np.int32), qo)
+    for q in np.unique(np.concatenate([[0, 63, 64, 127, 128, 49151, 49152], rng.choice(Q, 60)])):
+        od = oracle.decide(E_op[qr[q]].astype(np.float64), E_dev[qr[q]].astype(np.float64), masks, opts,
+                           qo[q:q + 1], w, f=256, dec_hidden=256, n_dev=9)
+        if decide_gap_ok(od["prior"][0], od["best"][0], 1e-5):
+            assert res["argmax"][q] == od["argmax"][0], q
+        np.testing.assert_allclose(res["best"][q], od["best"][0], rtol=1e-5, atol=1e-5)
+        np.testing.assert_allclose(res["prior"][q], od["prior"][0], rtol=1e-4, atol=1e-7)
     g.close()
 
 

@@ -256,6 +256,40 @@ def test_train_argument_checks(torch):
     assert e.value.status == _abi.TAG_ENOSPACE
 
 
+@pytest.mark.parametrize("f,n_op,R", [(256, 410, 120), (128, 820, 120)])
+def test_train_step_batch_is_the_mean_of_its_halves(torch, f, n_op, R):
+    """49,200 rows at f = 256 and 98,400 at 128 (hidden-row gradients in 128 x 128 blocks, the last one ragged) against
+    the two halves of the batch (smaller blocks, other splits of the weight gradients): sums of up to 1e5 fp32 terms
+    in another order, 1e-5 of each array's norm."""
+    import paper_2302_06126_amd.train as PT
+    topo = synth.random_topology(78 + f, n_op, 3, 2 * n_op)
+    rng = np.random.default_rng((2302, 99, f))
+    w = synth.make_weights(f, 4, 1, 42, 32, bias_scale=0.3)
+    masks, opts = rng.integers(1, 8, 24).astype(np.uint64), rng.integers(0, 4, 24).astype(np.uint8)
+    target = rng.random((R, 24)) ** 4
+    target /= target.sum(axis=1, keepdims=True)
+    q_op = rng.integers(0, n_op, R)
+    x = [rng.uniform(-1, 1, (R, n_op, 42)).astype(np.float32), rng.uniform(-1, 1, (R, 3, 8)).astype(np.float32),
+         rng.uniform(-1, 1, topo.e_oo).astype(np.float32), rng.uniform(-1, 1, (R, topo.e_dd, 2)).astype(np.float32),
+         rng.integers(0, 2, (R, topo.e_od)).astype(np.uint8)]
+    g = P.Graph([topo])
+    mod = P.Model(w, f=f, heads=4, layers=1, f_op=42, dec_hidden=32)
+
+    def grads(a, b):
+        dev = [torch.from_numpy(v if i == 2 else np.ascontiguousarray(v[a:b])).cuda() for i, v in enumerate(x)]
+        tr = PT.Trainer(g, mod, b - a, masks, opts, np.arange(b - a), np.zeros(b - a), q_op[a:b])
+        tr.set_targets(target[a:b])
+        tr.step(P.make_features(*dev))
+        return {k: v.cpu().numpy().astype(np.float64) for k, v in tr.grads.items()}
+
+    whole, one, two = grads(0, R), grads(0, R // 2), grads(R // 2, R)
+    for k in whole:
+        if k != "dec_b2":   # (zero but for rounding)
+            err = np.linalg.norm(whole[k] - (one[k] + two[k]) / 2) / np.linalg.norm(whole[k])
+            assert err <= 1e-5, (k, err)
+    g.close()
+
+
 def test_long_weight_gradient_has_no_bias(torch):
     """The decoder's device weights, summed over 81,000 device rows of gradients of either sign.  Hidden units h and
     h + 64 have the same weights and opposite readouts, so the gradients of their rows are opposite bit for bit, and so

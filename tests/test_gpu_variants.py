@@ -43,7 +43,7 @@ def _features(topo, R, seed, shared_oo):
     return x_op, x_dev, x_oo, x_dd, x_od
 
 
-def _run(topo, R, f, heads, layers, relations, edge_act, heads_mode, seed=0, shared_oo=False):
+def _run(topo, R, f, heads, layers, relations, edge_act, heads_mode, seed=0, shared_oo=False, only=None):
     w = synth.make_weights(f, heads, layers, 42, f, bias_scale=0.3, seed_extra=seed, relations=relations,
                            heads_mode=heads_mode)
     x_op, x_dev, x_oo, x_dd, x_od = _features(topo, R, seed, shared_oo)
@@ -53,7 +53,7 @@ def _run(topo, R, f, heads, layers, relations, edge_act, heads_mode, seed=0, sha
     E_op, E_dev = P.forward(g, m, dev_tensor(x_op), dev_tensor(x_dev), dev_tensor(x_oo), dev_tensor(x_dd),
                             dev_tensor(x_od))
     worst = 0.0
-    for r in range(R):
+    for r in only or range(R):
         xo = x_oo if shared_oo else x_oo[r]
         R_op, R_dev = oracle.forward(topo, x_op[r], x_dev[r], xo, x_dd[r], x_od[r], w, f=f, heads=heads,
                                      layers=layers, relations=relations, edge_act=edge_act, heads_mode=heads_mode)
@@ -131,12 +131,15 @@ def test_variant_argument_checks():
     (130, 3, 2, 256, 1, 5, "affine", "avg"),
     (130, 3, 2, 256, 8, 3, "affine", "avg"),
     (3307, 2, 20, 64, 4, 5, "affine", "concat"),   # several rows per lane group, a ragged last group
+    (3307, 2, 20, 128, 2, 3, "affine", "avg"),     # ... 32 and 64 KiB of row sums
+    (3307, 2, 20, 256, 8, 5, "relu", "concat"),
 ])
 def test_variant_row_parts_and_groups(n_op, n_dev, R, f, heads, relations, edge_act, heads_mode):
     # ops linked to device 0 only, to all, or to none; the last device has few links (fewer parts than the first)
     od = [(u, j) for u in range(n_op) for j in range(n_dev) if j == 0 or (u % 3 == 0 and j < n_dev - 1) or u == 5]
     topo = mk_topo(n_op, n_dev, oo=[(i, i + 1) for i in range(n_op - 1) if i % 7], dd=[(0, 1)], od=od)
-    err = _run(topo, R, f, heads, 2, relations, edge_act, heads_mode, seed=n_op, shared_oo=relations == 3)
+    err = _run(topo, R, f, heads, 2, relations, edge_act, heads_mode, seed=n_op, shared_oo=relations == 3,
+               only=(0, R // 2, R - 1) if R * f > 2000 else None)
     say(f"n_op={n_op} R={R} f={f} K={heads} {relations} {edge_act} {heads_mode}: {err:.2e}")
 
 
