@@ -142,8 +142,12 @@ void tag_graph_destroy(tag_graph *g);
  *   f_dev       raw device feature width, 1..64
  *   dec_hidden  decoder hidden width H: 0 = a single linear Dense layer,
  *               else 1..1024 (Dense + ReLU + scalar readout)
- *   dtype       TAG_F32: everything fp32.  TAG_BF16: the relation transforms
- *               W^h h take bf16 operands (round-to-nearest-even) with fp32
+ *   dtype       TAG_F32: fp32 storage, operands and accumulation; the wide
+ *               contractions multiply exact three-way bf16 splits of their
+ *               fp32 operands, as near the exact sums as fp32 products (in the
+ *               relation transforms an infinite hidden value gives NaN).
+ *               TAG_BF16: the relation transforms W^h h take bf16 operands
+ *               (round-to-nearest-even) with fp32
  *               accumulation and store W^h h and the hidden embeddings in
  *               bf16; attention and aggregation stay fp32.
  *   gamma_same  gamma for op-op and device-device links (paper: 1)
