@@ -614,7 +614,9 @@ tag_status decide_run(const tag_graph *g, const tag_model_dims *dims, const tag_
     A.q_rep = query_rep; A.q_graph = query_graph; A.q_op = query_op;
     A.t = L.t; A.u = L.u; A.v = L.v;
     A.argmax = argmax; A.best = best_score; A.prior = prior; A.dec = decision;
-    const bool group = A.Q >= kGroupMinQ && H > 0 && H <= kGroupMaxH && A.S <= kGroupMaxS;
+    // (one query per candidate, as a search asks, has nothing to share: 8,192 of them, H = 64, 320 us with four
+    // queries per block, 328 in groups)
+    const bool group = A.Q >= kGroupMinQ && A.Q >= 2 * (int64_t)A.R && H > 0 && H <= kGroupMaxH && A.S <= kGroupMaxS;
     A.bound = group ? 1 : 0;
     prof_begin(TAG_STAGE_DECIDE, stream);
     launch_projections(A, L.qrow, stream);
