@@ -499,13 +499,18 @@ size_t carve_var(const tag_graph *g, const tag_model_dims *d, int32_t R, void *b
     }
     L->U = c.take<float>((size_t)d->layers * NR * F * 2);
     L->cp = c.take<float>((size_t)d->layers * NR * F);
-    for (int i = 0; i < 2; ++i) {   // tables sized for per-replica features (the caller's strides decide at run time)
-        L->te_oo[i] = table && (i == 0 || five) ? c.take<float>((size_t)R * g->e_oo * F + 1) : nullptr;
-        L->te_od[i] = table && (i == 0 || five) ? c.take<float>(2 * F) : nullptr;
+    const int64_t rec = d->head_mode == 1 ? var_rec<true>(d->f, d->heads) : var_rec<false>(d->f, d->heads);
+    // a layer's op-op tables have been read when its device rows' parts are written: one place for both
+    // (tables sized for per-replica features: the caller's strides decide at run time)
+    const size_t oo = table ? (size_t)R * g->e_oo * F : 0, parts = M * var_parts(g) * rec;
+    float *p = c.take<float>(std::max((five ? 2 : 1) * oo, parts) + 1);
+    L->part = p;
+    for (int i = 0; i < 2; ++i) {
+        const bool on = table && (i == 0 || five);
+        L->te_oo[i] = on ? p + i * oo : nullptr;
+        L->te_od[i] = on ? c.take<float>(2 * F) : nullptr;
     }
     L->te_dd = table ? c.take<float>((size_t)R * g->e_dd * F + 1) : nullptr;
-    const int64_t rec = d->head_mode == 1 ? var_rec<true>(d->f, d->heads) : var_rec<false>(d->f, d->heads);
-    L->part = c.take<float>(M * var_parts(g) * rec + 1);
     return c.used;
 }
 

@@ -143,6 +143,20 @@ def test_variant_row_parts_and_groups(n_op, n_dev, R, f, heads, relations, edge_
     say(f"n_op={n_op} R={R} f={f} K={heads} {relations} {edge_act} {heads_mode}: {err:.2e}")
 
 
+def test_variant_row_parts_take_no_scratch_beside_tables():
+    # records of device rows (8 averaged heads: 8 f + 16 floats each) go where the layer's op-op tables were
+    g = P.Graph([mk_topo(1200, 16, oo=[(i, i + 1) for i in range(1199)] + [(i, i + 3) for i in range(0, 1196, 3)],
+                         dd=[(i, j) for i in range(16) for j in range(i)],
+                         od=[(u, j) for u in range(1200) for j in range(16)])])
+    need = {}
+    for head_mode in (0, 1):
+        d = P._abi.tag_model_dims(128, 8, 2, 42, 8, 64, P.TAG_F32, 1.0, 0.1, 0.2, 0, 5, 1, head_mode)
+        st, need[head_mode] = P.tag_gnn_workspace(g.handle, d, 8)
+        assert st == P._abi.TAG_OK
+    assert need[1] <= 1.01 * need[0], need
+    g.close()
+
+
 def test_variant_union_of_topologies():
     # replicas of two unlike topologies: row ranges cross both topology and replica ends
     topos = [mk_topo(n, m, oo=[(i, i + 2) for i in range(n - 2)], dd=[(0, m - 1)],
